@@ -13,6 +13,8 @@
 // The attention step is pace_vit_attention over the windows.
 #include <math.h>
 
+#include <type_traits>
+
 #include "pace_internal.h"
 
 namespace pace {
@@ -27,6 +29,19 @@ __device__ __forceinline__ uint16_t to_bf16(float f) {
   return static_cast<uint16_t>(u >> 16);
 }
 __device__ __forceinline__ float from_bf16(uint16_t b) { return __uint_as_float(static_cast<uint32_t>(b) << 16); }
+
+__device__ __forceinline__ uint32_t pack2(float a, float b) {   // two bf16, nearest even
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  const f32x2 v = {a, b};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+// x / (1 + exp(-x)) on the exponential and reciprocal units: within 2^-20 of the value, which the
+// bf16 rounding that follows (2^-9) hides; with expf and a division the 64 of a lane cost as much
+// as a tenth of the product
+__device__ __forceinline__ float silu(float x) {
+  return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(x * -1.4426950408889634f));
+}
 
 // ---------------------------------------------------------------- patchify
 __global__ __launch_bounds__(256) void preview_patchify(const uint8_t* __restrict__ img, int W, int P, int gw,
@@ -48,122 +63,263 @@ __global__ __launch_bounds__(256) void preview_patchify(const uint8_t* __restric
 }
 
 // ---------------------------------------------------------------- GEMM
-// C[M, N] = A[M, K] B[N, K]^T.  A 128x128 output tile per workgroup, 4 waves of 64x64 (2x2
-// MFMA tiles of 32x32), K in steps of 32 through LDS, double buffered: the global loads of step
-// t+1 are in flight while step t is multiplied.  Rows past M or N and columns past K load as
-// zeros (range-checked buffer loads), so tails need no branches.
-constexpr int kGM = 128, kGN = 128, kGK = 32;
-constexpr int kGS = kGK + 8;   // LDS row stride (elements)
+// C[M, N] = A[M, K] B[N, K]^T.  WM x WN waves, each with MI x NI MFMA tiles of 32 x 32.  K goes in
+// stages of 32 through a ring of ST LDS buffers filled by DMA (buffer to LDS, no registers):
+// stage t + ST - 1 is requested while stage t is multiplied, and the barrier of stage t waits
+// for stage t + 1 only, so a load has ST - 2 stages to arrive.  The fragments of the next half
+// stage are read among the MFMAs of the present one, also across the barrier.  Rows past M or N
+// and chunks past K load as zeros (range check, out-of-range offsets), so tails need no branches.
+//   A stage row holds four 16-byte chunks; chunk c of row r sits in slot c ^ ((r >> 2) & 3), so
+// that the 32 rows that a fragment read touches spread over all LDS banks.  The DMA writes lanes
+// in order, so the swizzle is in the global addresses.
+//   The product is formed as C^T (B's rows are the MFMA's A operand): a lane then holds four
+// neighbouring columns of one row, which makes SwiGLU's gate and up neighbours in one lane; the
+// tile leaves through LDS so that rows are stored in 16-byte chunks, and a residual tile comes
+// the same way (read straight into the lanes it cost 20 us of a 64-us round of tiles).
+//   Bound: MFMA.  What is left is the last round of tiles, the burst of stores (and residual
+// loads) when a round ends, and about a third of the issue slots in the loop: one stage of a
+// 256 x 256 tile takes 0.85-0.9 us for 1,024 MFMA cycles per SIMD.  Measured against the 128 x 128
+// register-staged kernel before it, 42,196 rows: N = K = 1,280 with residual 337 -> 214 us; N =
+// 6,848, K = 1,280 with SwiGLU 1,211 -> 742 us (997 TFLOP/s); N = 1,280, K = 3,424 with residual 661
+// -> 454 us; 8,192^3 1,590 -> 941 us (1,169 TFLOP/s).  Tried on the same shapes: 4 x 4 MFMA tiles
+// per wave with four waves (1,080 TFLOP/s at 8,192^3: one wave per SIMD does not hide its own LDS
+// reads), two 128 x 256 workgroups per CU with a ring of three (1,022), no fragments ahead of the
+// barrier (1,144).
+constexpr int kGK = 32;                      // K per stage
 
 enum { kEpiBias = 0, kEpiResidual = 1, kEpiSwiglu = 2 };
 
 struct GemmParams {
   const uint16_t* A;
-  const uint16_t* B;
-  const float* bias;     // [N] or null
-  const uint16_t* R;     // residual [M, N] (kEpiResidual)
-  uint16_t* C;           // [M, N], or [M, N / 2] for kEpiSwiglu
+  const uint16_t* B[3];     // up to three products of the same A and shape (grid z)
+  const float* bias[3];     // [N] or null
+  const uint16_t* R;        // residual [M, N] (kEpiResidual)
+  uint16_t* C[3];           // [M, N], or [M, N / 2] for kEpiSwiglu
   int M, N, K;
-  int lda, ldb, ldc, ldr;
+  int tiles_m, tiles_n;
   int mode;
+  int vec;                  // C (and R) rows are 16-byte aligned: stored in 16-byte chunks
 };
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t grsrc(const void* base, unsigned bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, 0x00020000);
-}
+typedef __attribute__((address_space(3))) const char g_lds_char;
+typedef int gi32x4 __attribute__((ext_vector_type(4)));
 constexpr unsigned kGOut = 0x7FFFFFF0u;
 
-__global__ __launch_bounds__(256, 2) void gemm_bf16_nt(const GemmParams p) {
-  __shared__ __align__(16) uint16_t As[2][kGM * kGS];
-  __shared__ __align__(16) uint16_t Bs[2][kGN * kGS];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+__device__ __forceinline__ gi32x4 g_rsrc(const void* base, unsigned bytes) {
+  const unsigned long long a = reinterpret_cast<unsigned long long>(base);
+  gi32x4 r;
+  r.x = __builtin_amdgcn_readfirstlane(static_cast<int>(a & 0xffffffffull));
+  r.y = __builtin_amdgcn_readfirstlane(static_cast<int>((a >> 32) & 0xffffull));   // stride 0
+  r.z = __builtin_amdgcn_readfirstlane(static_cast<int>(bytes));
+  r.w = 0x00020000;
+  return r;
+}
+// 64 lanes x 16 bytes from the buffer to lds .. lds + 1023; untracked by the compiler, awaited
+// with g_wait.
+__device__ __forceinline__ void g_dma16(gi32x4 r, unsigned lds, unsigned voff) {
+  const unsigned m0 = __builtin_amdgcn_readfirstlane(lds);
+  asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
+               :: "v"(voff), "s"(r), "{m0}"(m0) : "memory");
+}
+template <int N>
+__device__ __forceinline__ void g_wait() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
+
+// Workgroup barrier without the wait for LDS reads in flight: the buffers that they read are
+// overwritten only two barriers later.
+__device__ __forceinline__ void g_barrier() { asm volatile("s_barrier" ::: "memory"); }
+
+template <int MI, int NI, int WM, int WN, int ST>
+__global__ __launch_bounds__(64 * WM * WN, MI * NI > 8 ? 1 : 2) void gemm_bf16_nt(const GemmParams p) {
+  constexpr int BM = 32 * MI * WM, BN = 32 * NI * WN;
+  constexpr int NW = WM * WN, kGThreads = 64 * NW;
+  constexpr int kStage = (BM + BN) * kGK;            // elements per stage
+  constexpr int kInst = (BM + BN) / 16;              // wave-wide DMAs per stage, 16 rows each
+  constexpr int kPW = kInst / NW;              // per wave
+  static_assert(kInst % NW == 0, "every wave issues the same DMAs");
+  constexpr int kLds = ST * kStage > BM * BN ? ST * kStage : BM * BN;
+  __shared__ __align__(16) uint16_t lds[kLds];
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 5, c32 = lane & 31;
-  const int bm = blockIdx.y * kGM, bn = blockIdx.x * kGN;
-  const int wm = (w >> 1) * 64, wn = (w & 1) * 64;
-  const auto ra = grsrc(p.A, static_cast<unsigned>(static_cast<long long>(p.M) * p.lda * 2));
-  const auto rb = grsrc(p.B, static_cast<unsigned>(static_cast<long long>(p.N) * p.ldb * 2));
-  // this thread's two 16-byte chunks of each tile: chunk c = tid + 256 u -> row c / 4, k chunk c % 4
-  int arow[2], brow[2], kc[2];
+  const int wm = (w / WN) * 32 * MI, wn = (w % WN) * 32 * NI;
+  // XCD-contiguous order; groups of eight row tiles column by column, so that the workgroups
+  // that run together on an XCD share a few rows of A and a few of B in its L2
+  const int per = p.tiles_m * p.tiles_n;
+  const int lb = remap_block_id(blockIdx.x, gridDim.x);
+  const int z = lb / per;
+  const int tl = lb - z * per;
+  const int gsz = 8 * p.tiles_n, grp = tl / gsz, in = tl - grp * gsz;
+  const int gm = min(8, p.tiles_m - 8 * grp);
+  const int tn = in / gm, tm = 8 * grp + (in - tn * gm);
+  const int bm = tm * BM, bn = tn * BN;
+  const gi32x4 ra = g_rsrc(p.A, static_cast<unsigned>(static_cast<long long>(p.M) * p.K * 2));
+  const gi32x4 rb = g_rsrc(p.B[z], static_cast<unsigned>(static_cast<long long>(p.N) * p.K * 2));
+
+  // this lane's chunk of DMA i (wave w issues i = w, w + 8, ...; the first BM / 16 are A's rows)
+  unsigned off[kPW];
+  int kc = 0;   // first k of the lane's chunk, the same in each: row >> 2 depends on the lane only
+  {
+    const int slot = lane & 3, r16 = lane >> 2;
+    kc = (slot ^ ((r16 >> 2) & 3)) * 8;
 #pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int c = tid + 256 * u;
-    arow[u] = c >> 2;
-    brow[u] = c >> 2;
-    kc[u] = (c & 3) * 8;
+    for (int u = 0; u < kPW; ++u) {
+      const int i = w + NW * u;
+      const bool isa = i < BM / 16;
+      const int row = isa ? bm + i * 16 + r16 : bn + (i - BM / 16) * 16 + r16;
+      // rows past the end lie past the buffer's range
+      off[u] = row < (isa ? p.M : p.N) ? static_cast<unsigned>((static_cast<long long>(row) * p.K + kc) * 2) : kGOut;
+    }
   }
-  auto load = [&](int k0, uint4* va, uint4* vb) __attribute__((always_inline)) {
+  const unsigned lds0 = static_cast<unsigned>(reinterpret_cast<unsigned long long>((g_lds_char*)(const void*)lds));
+  auto load = [&](int t, int buf) __attribute__((always_inline)) {
+    const bool in_k = t * kGK + kc < p.K;
+    const unsigned base = lds0 + buf * (kStage * 2);
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int k = k0 + kc[u];
-      const bool kok = k < p.K;
-      const int ma = bm + arow[u], nb = bn + brow[u];
-      const unsigned oa = (kok && ma < p.M) ? static_cast<unsigned>((static_cast<long long>(ma) * p.lda + k) * 2) : kGOut;
-      const unsigned ob = (kok && nb < p.N) ? static_cast<unsigned>((static_cast<long long>(nb) * p.ldb + k) * 2) : kGOut;
-      va[u] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(ra, oa, 0, 0));
-      vb[u] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rb, ob, 0, 0));
+    for (int u = 0; u < kPW; ++u) {
+      const int i = w + NW * u;
+      const unsigned o = in_k ? off[u] + static_cast<unsigned>(t) * (kGK * 2) : kGOut;
+      g_dma16(i < BM / 16 ? ra : rb, base + i * 1024, o);
     }
   };
-  auto store = [&](int buf, const uint4* va, const uint4* vb) __attribute__((always_inline)) {
+  // fragment reads: row r of the stage at byte 64 r, chunk c in slot c ^ ((r >> 2) & 3)
+  const int s0 = (g ^ ((c32 >> 2) & 3)) * 8;   // half stage 0; half stage 1 is s0 ^ 16 (elements)
+  auto frags = [&](int buf, int kk, gbf16x8* a, gbf16x8* b) __attribute__((always_inline)) {
+    const uint16_t* st = lds + buf * kStage + c32 * kGK + (kk ? (s0 ^ 16) : s0);
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      *reinterpret_cast<uint4*>(&As[buf][arow[u] * kGS + kc[u]]) = va[u];
-      *reinterpret_cast<uint4*>(&Bs[buf][brow[u] * kGS + kc[u]]) = vb[u];
+    for (int j = 0; j < NI; ++j) b[j] = *reinterpret_cast<const gbf16x8*>(st + (BM + wn + 32 * j) * kGK);
+#pragma unroll
+    for (int i = 0; i < MI; ++i) a[i] = *reinterpret_cast<const gbf16x8*>(st + (wm + 32 * i) * kGK);
+  };
+  gf32x16 acc[MI][NI];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NI; ++j) acc[i][j] = gf32x16{};
+  auto mul = [&](const gbf16x8* a, const gbf16x8* b) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NI; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[j], a[i], acc[i][j], 0, 0, 0);
+  };
+  // request: fragment reads spread among the MFMAs before the ones that use them
+  auto spread = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < MI * NI; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      if (i < MI + NI) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
     }
   };
-  gf32x16 acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = gf32x16{};
+
   const int nk = (p.K + kGK - 1) / kGK;
-  uint4 va[2], vb[2];
-  load(0, va, vb);
-  store(0, va, vb);
-  __syncthreads();
-  for (int t = 0; t < nk; ++t) {
-    const int buf = t & 1;
-    if (t + 1 < nk) load((t + 1) * kGK, va, vb);
+  // requested before stage 0: stages 0 .. ST - 2
 #pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-      gbf16x8 a[2], b[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        a[i] = *reinterpret_cast<const gbf16x8*>(&As[buf][(wm + 32 * i + c32) * kGS + kk * 16 + g * 8]);
-        b[i] = *reinterpret_cast<const gbf16x8*>(&Bs[buf][(wn + 32 * i + c32) * kGS + kk * 16 + g * 8]);
-      }
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+  for (int s = 0; s < ST - 1; ++s)
+    if (s < nk) load(s, s);
+  gbf16x8 a0[MI], b0[NI], a1[MI], b1[NI];
+  int cur = 0;   // buffer of stage t
+  auto next = [](int b) { return b == ST - 1 ? 0 : b + 1; };
+  if (nk >= ST - 1) g_wait<(ST - 2) * kPW>(); else g_wait<0>();
+  g_barrier();
+  frags(0, 0, a0, b0);
+  // stage t: its first half is in a0 / b0.  Past the barrier stage t + 1 is in LDS and every
+  // wave is done with stage t - 1, whose buffer stage t + ST - 1 takes.
+  auto stage = [&](int t, auto LAST) __attribute__((always_inline)) {
+    constexpr bool last = decltype(LAST)::value;
+    if constexpr (!last) {
+      if (t + ST - 2 < nk) g_wait<(ST - 3) * kPW>(); else g_wait<0>();
+      g_barrier();
+      if (t + ST - 1 < nk) load(t + ST - 1, cur == 0 ? ST - 1 : cur - 1);
     }
-    if (t + 1 < nk) store(buf ^ 1, va, vb);
+    __builtin_amdgcn_sched_barrier(0);
+    frags(cur, 1, a1, b1);
+    mul(a0, b0);
+    spread();
+    __builtin_amdgcn_sched_barrier(0);
+    cur = next(cur);
+    if constexpr (!last) frags(cur, 0, a0, b0);
+    mul(a1, b1);
+    if constexpr (!last) spread();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  for (int t = 0; t + 1 < nk; ++t) stage(t, std::false_type{});
+  stage(nk - 1, std::true_type{});
+
+  // epilogue: register 4 jj + ii of tile (i, j) is row wm + 32 i + c32, column
+  // wn + 32 j + 8 jj + 4 g + ii.  The bf16 tile goes through LDS, once every wave has read its
+  // last stage: 16-byte chunk ch of row r in slot ch ^ (r mod the chunks of a row), so that the
+  // 32 rows of a write spread over all banks.  A residual tile comes in the same way first.
+  __syncthreads();
+  const int mode = p.mode;
+  const bool glu = mode == kEpiSwiglu;
+  constexpr int kCh = BN / 8;
+  const bool res_lds = mode == kEpiResidual && p.vec;
+  if (res_lds) {
+    constexpr int kRows = 512 / BN;   // tile rows per wave-wide DMA
+    const gi32x4 rr = g_rsrc(p.R + static_cast<long long>(bm) * p.N, static_cast<unsigned>(min(BM, p.M - bm)) * p.N * 2u);
+#pragma unroll
+    for (int u = 0; u < BM / kRows / NW; ++u) {
+      const int i = w + NW * u, r = i * kRows + lane / kCh;
+      const int n = bn + (((lane % kCh) ^ (r & (kCh - 1))) * 8);
+      g_dma16(rr, lds0 + i * 1024, n < p.N ? static_cast<unsigned>(r * p.N + n) * 2u : kGOut);
+    }
+    g_wait<0>();
     __syncthreads();
   }
-  // epilogue: register 4 jj + ii of tile (i, j) is row wm + 32 i + 8 jj + 4 g + ii, column
-  // wn + 32 j + c32
+  const auto rbias = range_rsrc(p.bias[z], p.bias[z] != nullptr ? static_cast<unsigned>(p.N) * 4u : 0u);
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  f32x4 bv[NI][4];
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int n = bn + wn + 32 * j + c32;
-    const float bias = (p.bias != nullptr && n < p.N) ? p.bias[n] : 0.f;
+  for (int j = 0; j < NI; ++j)
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int jj = 0; jj < 4; ++jj)
+      bv[j][jj] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+          rbias, static_cast<unsigned>(bn + wn + 32 * j + 8 * jj + 4 * g) * 4u, 0, 0));
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = bm + wm + 32 * i + 8 * (r >> 2) + 4 * g + (r & 3);
-        float v = acc[i][j][r] + bias;
-        if (p.mode == kEpiSwiglu) {
-          // columns 2f (gate) and 2f + 1 (up) sit in neighbouring lanes
-          const float other = __shfl_xor(v, 1, 64);
-          if ((c32 & 1) == 0 && m < p.M && n < p.N) {
-            const float gate = v, up = other;
-            p.C[static_cast<long long>(m) * p.ldc + (n >> 1)] = to_bf16(gate / (1.0f + expf(-gate)) * up);
+  for (int j = 0; j < NI; ++j)
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) {
+      const int cl = wn + 32 * j + 8 * jj + 4 * g, n = bn + cl;
+#pragma unroll
+      for (int i = 0; i < MI; ++i) {
+        const int rl = wm + 32 * i + c32;
+        float v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = acc[i][j][4 * jj + q] + bv[j][jj][q];
+        if (glu) {
+          const int cg = cl >> 1;
+          *reinterpret_cast<uint32_t*>(&lds[rl * (BN / 2) + (((cg >> 3) ^ (rl & (kCh / 2 - 1))) << 3) + (cg & 7)]) =
+              pack2(silu(v[0]) * v[1], silu(v[2]) * v[3]);
+        } else {
+          uint2* at = reinterpret_cast<uint2*>(&lds[rl * BN + (((cl >> 3) ^ (rl & (kCh - 1))) << 3) + (cl & 7)]);
+          if (res_lds) {
+            const uint2 u = *at;
+            v[0] += __uint_as_float(u.x << 16); v[1] += __uint_as_float(u.x & 0xffff0000u);
+            v[2] += __uint_as_float(u.y << 16); v[3] += __uint_as_float(u.y & 0xffff0000u);
+          } else if (mode == kEpiResidual && bm + rl < p.M) {
+            const uint16_t* r = p.R + static_cast<long long>(bm + rl) * p.N + n;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+              if (n + q < p.N) v[q] += from_bf16(r[q]);
           }
-        } else if (m < p.M && n < p.N) {
-          if (p.mode == kEpiResidual) v += from_bf16(p.R[static_cast<long long>(m) * p.ldr + n]);
-          p.C[static_cast<long long>(m) * p.ldc + n] = to_bf16(v);
+          *at = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
         }
       }
+    }
+  __syncthreads();
+  const int nc = glu ? p.N / 2 : p.N, n0 = glu ? bn / 2 : bn;   // columns of C, the tile's first
+  const int cpr = glu ? kCh / 2 : kCh, cbits = __builtin_ctz(cpr);
+  uint16_t* C = p.C[z];
+  for (int c = tid; c < BM * cpr; c += kGThreads) {
+    const int r = c >> cbits, ch = c & (cpr - 1);
+    const int m = bm + r, n = n0 + ch * 8;
+    if (m >= p.M || n >= nc) continue;
+    uint16_t* dst = C + static_cast<long long>(m) * nc + n;
+    const uint16_t* src = &lds[(r * cpr + (ch ^ (r & (cpr - 1)))) * 8];
+    if (p.vec) {
+      *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(src);
+    } else {
+      for (int q = 0; q < 8 && n + q < nc; ++q) dst[q] = src[q];
+    }
   }
 }
 
@@ -206,9 +362,58 @@ __global__ __launch_bounds__(256) void rmsnorm_bf16(const uint16_t* __restrict__
   }
 }
 
-pace_status_t launch_gemm(const GemmParams& p, hipStream_t stream) {
-  dim3 grid((p.N + kGN - 1) / kGN, (p.M + kGM - 1) / kGM);
-  hipLaunchKernelGGL(gemm_bf16_nt, grid, dim3(256), 0, stream, p);
+// What every product needs; nothing is launched otherwise.
+pace_status_t check_gemm(const GemmParams& p, int nz) {
+  PACE_REQUIRE(p.M >= 1 && p.N >= 1 && p.K >= 8 && p.K % 8 == 0,
+               "pace_gemm_bf16: M=%d N=%d K=%d (K a positive multiple of 8)", p.M, p.N, p.K);
+  PACE_REQUIRE(aligned16(p.A), "pace_gemm_bf16: A and B must be 16-byte aligned");
+  for (int z = 0; z < nz; ++z) PACE_REQUIRE(aligned16(p.B[z]), "pace_gemm_bf16: A and B must be 16-byte aligned");
+  PACE_REQUIRE(static_cast<long long>(p.M) * p.K * 2 < (1ll << 30) && static_cast<long long>(p.N) * p.K * 2 < (1ll << 30),
+               "pace_gemm_bf16: an operand spans 1 GiB or more");
+  return PACE_OK;
+}
+
+template <int MI, int NI, int WM, int WN, int ST>
+void launch_tile(GemmParams p, int nz, hipStream_t stream) {
+  p.tiles_m = (p.M + 32 * MI * WM - 1) / (32 * MI * WM);
+  p.tiles_n = (p.N + 32 * NI * WN - 1) / (32 * NI * WN);
+  const dim3 grid(static_cast<unsigned>(p.tiles_m) * p.tiles_n * nz);
+  hipLaunchKernelGGL((gemm_bf16_nt<MI, NI, WM, WN, ST>), grid, dim3(64 * WM * WN), 0, stream, p);
+}
+
+// Tiles of 256 x 256 (one workgroup per CU) use the matrix cores best, but come in rounds of 256;
+// tiles of 64 x 128 fill the chip from small products on.  On 42,196 x 1,280 x 1,280 the large
+// tiles ran 4 rounds of 52 us at 640 TFLOP/s against 452 TFLOP/s with the small ones; on
+// 1,024 x 1,280 x 1,280 (20 large tiles) 32.5 us against 12.3.  So one round of large tiles costs
+// as much as about 156 of them in small ones, and a launch of small ones at least 0.3 of a round.
+// The rows go to whichever of these is the shortest: large tiles alone, small ones alone, or the
+// full rounds in large and the remaining rows in small tiles.
+pace_status_t launch_gemm(GemmParams p, int nz, hipStream_t stream) {
+  const int nc = p.mode == kEpiSwiglu ? p.N / 2 : p.N;
+  p.vec = nc % 8 == 0 && p.N < (1 << 20);   // a tile's rows of C and R within one buffer's range
+  for (int z = 0; z < nz; ++z) p.vec = p.vec && aligned16(p.C[z]);
+  if (p.mode == kEpiResidual) p.vec = p.vec && aligned16(p.R);
+  const long long rows = (p.M + 255) / 256, per_row = ((p.N + 255) / 256) * static_cast<long long>(nz);
+  auto small_cost = [&](long long r) { return r <= 0 ? 0.0 : fmax(0.3, static_cast<double>(r * per_row) / 156.0); };
+  auto cost = [&](long long r) { return static_cast<double>((r * per_row + 255) / 256) + small_cost(rows - r); };
+  const long long full = rows * per_row / 256 * 256 / per_row;   // row tiles in full rounds
+  long long best = 0;
+  if (cost(full) + 0.1 < cost(best)) best = full;
+  if (cost(rows) <= cost(best) + 0.15) best = rows;
+  const int m0 = static_cast<int>(best * 256 < p.M ? best * 256 : p.M);
+  if (m0 > 0) {
+    GemmParams q = p;
+    q.M = m0;
+    launch_tile<4, 2, 2, 4, 4>(q, nz, stream);
+  }
+  if (m0 < p.M) {
+    GemmParams q = p;
+    q.M = p.M - m0;
+    q.A += static_cast<long long>(m0) * p.K;
+    if (q.R != nullptr) q.R += static_cast<long long>(m0) * p.N;
+    for (int z = 0; z < nz; ++z) q.C[z] += static_cast<long long>(m0) * nc;
+    launch_tile<2, 1, 1, 4, 6>(q, nz, stream);
+  }
   return check_launch("gemm_bf16_nt");
 }
 
@@ -222,20 +427,15 @@ extern "C" {
 pace_status_t pace_gemm_bf16(const uint16_t* A, const uint16_t* B, const float* bias, const uint16_t* residual,
                              uint16_t* C, int M, int N, int K, int epilogue, hipStream_t stream) {
   PACE_REQUIRE(A && B && C, "pace_gemm_bf16: null device pointer");
-  PACE_REQUIRE(M >= 1 && N >= 1 && K >= 8 && K % 8 == 0,
-               "pace_gemm_bf16: M=%d N=%d K=%d (K a positive multiple of 8)", M, N, K);
-  PACE_REQUIRE(aligned16(A) && aligned16(B), "pace_gemm_bf16: A and B must be 16-byte aligned");
   PACE_REQUIRE(epilogue >= 0 && epilogue <= 2, "pace_gemm_bf16: epilogue %d not in {0, 1, 2}", epilogue);
   PACE_REQUIRE(epilogue != 1 || residual != nullptr, "pace_gemm_bf16: residual epilogue without residual");
   PACE_REQUIRE(epilogue != 2 || N % 2 == 0, "pace_gemm_bf16: SwiGLU needs an even N");
-  PACE_REQUIRE(static_cast<long long>(M) * K * 2 < (1ll << 30) && static_cast<long long>(N) * K * 2 < (1ll << 30),
-               "pace_gemm_bf16: an operand spans 1 GiB or more");
   GemmParams p{};
-  p.A = A; p.B = B; p.bias = bias; p.R = residual; p.C = C;
+  p.A = A; p.B[0] = B; p.bias[0] = bias; p.R = residual; p.C[0] = C;
   p.M = M; p.N = N; p.K = K;
-  p.lda = K; p.ldb = K; p.ldc = (epilogue == 2) ? N / 2 : N; p.ldr = N;
   p.mode = epilogue;
-  return launch_gemm(p, stream);
+  const pace_status_t st = check_gemm(p, 1);
+  return st != PACE_OK ? st : launch_gemm(p, 1, stream);
 }
 
 size_t pace_apc_preview_workspace_size(int N, int dim, int ffn, int patch) {
@@ -295,9 +495,16 @@ pace_status_t pace_apc_preview(const uint8_t* img, int H, int W, int patch, cons
   if ((st = pace_gemm_bf16(X, w->pe, nullptr, nullptr, h0, N, D, kp, 0, stream)) != PACE_OK) return st;
   hipLaunchKernelGGL(rmsnorm_bf16, dim3((N + 3) / 4), dim3(256), 0, stream, h0, w->g1, u, N, D, 1e-6f);
   if ((st = check_launch("rmsnorm_bf16")) != PACE_OK) return st;
-  if ((st = pace_gemm_bf16(u, w->wq, w->bq, nullptr, q, N, D, D, 0, stream)) != PACE_OK) return st;
-  if ((st = pace_gemm_bf16(u, w->wk, w->bk, nullptr, k, N, D, D, 0, stream)) != PACE_OK) return st;
-  if ((st = pace_gemm_bf16(u, w->wv, w->bv, nullptr, v, N, D, D, 0, stream)) != PACE_OK) return st;
+  // q, k and v in one launch: three times the tiles, so a smaller part of the last round is idle
+  GemmParams g{};
+  g.A = u;
+  g.B[0] = w->wq; g.B[1] = w->wk; g.B[2] = w->wv;
+  g.bias[0] = w->bq; g.bias[1] = w->bk; g.bias[2] = w->bv;
+  g.C[0] = q; g.C[1] = k; g.C[2] = v;
+  g.M = N; g.N = D; g.K = D;
+  g.mode = kEpiBias;
+  if ((st = check_gemm(g, 3)) != PACE_OK) return st;
+  if ((st = launch_gemm(g, 3, stream)) != PACE_OK) return st;
   if ((st = pace_vit_attention(q, k, v, N, D / 80, 80, cu_windows, nwin, max_window, 1.0f / sqrtf(80.f), o,
                                nullptr, nullptr, nullptr, 0, stream)) != PACE_OK)
     return st;

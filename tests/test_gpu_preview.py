@@ -24,7 +24,12 @@ def _silu(x):
 
 
 @pytest.mark.parametrize("M,N,K,epi", [(300, 200, 72, 0), (1024, 1280, 1280, 0), (129, 257, 8, 1),
-                                       (513, 384, 592, 1), (200, 96, 1280, 2), (1, 2, 16, 2)])
+                                       (513, 384, 592, 1), (200, 96, 1280, 2), (1, 2, 16, 2),
+                                       # large tiles alone; full rounds of them and the remaining rows
+                                       # in small ones (bias, residual, residual at a row length that
+                                       # has no 16-byte chunks, SwiGLU); one and two stages of K
+                                       (10500, 1280, 64, 0), (15460, 1280, 72, 1), (15461, 1276, 40, 1),
+                                       (15460, 1280, 104, 2), (10241, 1290, 16, 2)])
 def test_gemm_epilogues(M, N, K, epi):
     from paper_2608_27206_amd import pace
     import torch
