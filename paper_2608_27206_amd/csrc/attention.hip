@@ -233,6 +233,7 @@ struct FwdParams {
   const int32_t* cu;       // [nseg + 1]
   int Ntot, Hq, Hkv, group;
   int nseg, nqt;           // q tiles per segment in the grid
+  int xcd_classes;         // gcd(Hkv, 8): classes of KV heads that own XCDs (causal order)
   float scale_log2;        // scale * log2(e)
   const uint16_t* vt;      // fp16 V^T tiles (rotation kernel only)
   long long vt_cols;
@@ -289,13 +290,34 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd(const FwdParams p) {
   __shared__ __align__(16) uint16_t Ks[2][kBN * C::KS];
   __shared__ __align__(16) uint16_t Vs[2][kBN * C::VS];
 
-  const int lb = remap_block_id(blockIdx.x, gridDim.x);
-  const int per_head = p.nseg * p.nqt;
-  const int h = lb / per_head;
-  const int rem = lb - h * per_head;
-  const int seg = rem / p.nqt;
-  int qt = rem - seg * p.nqt;
-  if (CAUSAL) qt = p.nqt - 1 - qt;   // longest causal rows first
+  int h, seg, qt;
+  if (CAUSAL) {
+    // Longest rows first on every XCD: workgroup b goes to XCD b % 8, and slot by slot each XCD
+    // takes the query tiles from the last to the first, all its heads and segments of one
+    // tile index together.  The KV heads of class c = kvh % g, g = gcd(Hkv, 8), belong to 8 / g
+    // XCDs, which take turns, so that the query heads of a KV head still share L2s.  (In one
+    // head after the other an XCD ended on the long rows of a head that it shares with the next
+    // XCD: 510 tile times against a mean of 418 in a list schedule of the 4K prefill's 28 heads
+    // over 84 query tiles, 434 in this order.  Measured: the 4K prefill with its text mass 875 ->
+    // 781 us, 1,183 tokens 32.2 -> 26.7 us.)
+    const int xpc = kNumXcd / p.xcd_classes;
+    const int xcd = blockIdx.x % kNumXcd, slot = blockIdx.x / kNumXcd;
+    const int c = xcd / xpc, pos = slot * xpc + (xcd - c * xpc);
+    const int heads = p.Hq / p.xcd_classes, m = p.nseg * heads;
+    const int level = pos / m, rem = pos - level * m;
+    if (level >= p.nqt) return;
+    qt = p.nqt - 1 - level;
+    seg = rem / heads;
+    const int hh = rem - seg * heads, kk = hh / p.group;
+    h = (kk * p.xcd_classes + c) * p.group + (hh - kk * p.group);
+  } else {
+    const int lb = remap_block_id(blockIdx.x, gridDim.x);
+    const int per_head = p.nseg * p.nqt;
+    h = lb / per_head;
+    const int rem = lb - h * per_head;
+    seg = rem / p.nqt;
+    qt = rem - seg * p.nqt;
+  }
   const int s0 = p.cu[seg];
   const int L = p.cu[seg + 1] - s0;
   const int q0 = qt * kBM;
@@ -1430,7 +1452,9 @@ pace_status_t launch_attention(FwdParams fp, bool causal, int max_seglen, const 
   }
   if (causal) {
     fp.nqt = (max_seglen + kBM - 1) / kBM;
-    hipLaunchKernelGGL((attn_fwd<D, true>), dim3(fp.nqt * fp.nseg * fp.Hq), dim3(kThreads), 0, stream, fp);
+    fp.xcd_classes = fp.Hkv % 8 == 0 ? 8 : fp.Hkv % 4 == 0 ? 4 : fp.Hkv % 2 == 0 ? 2 : 1;
+    const int xpc = kNumXcd / fp.xcd_classes, per_class = fp.nqt * fp.nseg * (fp.Hq / fp.xcd_classes);
+    hipLaunchKernelGGL((attn_fwd<D, true>), dim3(static_cast<unsigned>((per_class + xpc - 1) / xpc) * kNumXcd), dim3(kThreads), 0, stream, fp);
   } else if (D == 80 && max_seglen >= kRotMinSeg) {
     VtParams vp{};
     vp.v = fp.v; vp.vt = const_cast<uint16_t*>(fp.vt); vp.amax = const_cast<uint32_t*>(fp.vt_amax);
