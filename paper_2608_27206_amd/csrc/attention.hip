@@ -21,8 +21,8 @@
 //  attn_fwd_rot  the same computation for long segments at head dim 80, with 12 waves
 //             per workgroup in three groups that rotate through three phases (see the
 //             kernel), so that VALU and MFMA work of different waves overlap; its PV
-//             product runs in fp16 on V^T tiles that attn_vt_clear + attn_v_amax +
-//             attn_vt_prep write once per call (scaled per segment and KV head into fp16's
+//             product runs in fp16 on V^T tiles that attn_v_amax + attn_vt_prep write
+//             once per call (scaled per segment and KV head into fp16's
 //             range, a row of ones for the row sums).
 //
 //  attn_window  segments of at most 64 tokens (the 8x8-patch windows): O, LSE and the
@@ -121,7 +121,7 @@ constexpr unsigned kOutOfRange = 0x7FFFFFF0u;
 // is the wave's first row in it; rows at or past the segment end fall outside `ro` and are
 // dropped.  Every wave of the workgroup calls this once its last LDS read is behind a
 // workgroup barrier (the staging rows overlay the tile buffers).
-template <int D, int NT>
+template <int D, int NT, bool BARRIER = true>
 __device__ __forceinline__ void store_o_staged(const f32x16 (&oacc)[NT], float inv_l, int unshift,
                                                uint16_t* stage, __amdgpu_buffer_rsrc_t ro, int row0,
                                                int qstride) {
@@ -143,7 +143,8 @@ __device__ __forceinline__ void store_o_staged(const f32x16 (&oacc)[NT], float i
       }
     }
   }
-  __syncthreads();
+  if constexpr (BARRIER) __syncthreads();
+  else asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the wave reads only what it wrote itself
   typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 #pragma unroll
   for (int c = lane; c < 32 * CPR; c += 64) {
@@ -614,51 +615,63 @@ struct VtParams {
   const uint16_t* v;     // bf16 [N, H, 80]
   uint16_t* vt;          // fp16 [H, kVtRows, cols]
   uint32_t* amax;        // [nseg, H] largest |v| of each (segment, head), bf16 bits
+  uint32_t* part;        // the same of each token block: entry i of head h at i * part_i + h * part_h
+  long long part_i, part_h;
   const int32_t* cu;
-  int H, tiles;          // tiles: 64-column blocks per segment in the grid
+  int H, tiles;          // tiles: 64-column (or token) blocks per segment in the grid
+  int tok;               // tokens per block of attn_v_amax
+  int whole;             // a block is a whole segment: entry i is segment i
   long long cols;
 };
 
-// Clears the per-(segment, head) maxima (a kernel, not a memset, so that a captured graph
-// replays it like any other launch).
-__global__ __launch_bounds__(256) void attn_vt_clear(uint32_t* amax, int n) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < n) amax[i] = 0u;
+// Entry of token block b of segment s (starting at token c0): distinct for all blocks, and below
+// N / tok + nseg + 1.
+__device__ __forceinline__ int amax_entry(const VtParams& p, int c0, int s, int b) {
+  return p.whole ? s : c0 / p.tok + b + s;
 }
 
-// Largest |v| of every (segment, head): a workgroup reads kAmaxTok consecutive token rows of one
+// Largest |v| of every (token block, head): a workgroup reads p.tok consecutive token rows of one
 // segment ([tokens, H, 80] bf16, 16-byte chunks; consecutive threads read consecutive chunks),
-// keeps one maximum per chunk slot of a row, folds the 10 slots of each head through LDS and
-// raises the head's maximum with an atomic max on the bf16 bit pattern of |v| (monotone in |v|
-// for non-NaN values).
-constexpr int kAmaxTok = 128;
+// keeps one maximum per chunk slot of a row and folds the 10 slots of each head through LDS.  The
+// bf16 bit patterns of |v| order like the values (non-NaN).  attn_vt_prep takes the maximum over
+// a segment's blocks, so nothing has to be cleared first and no atomics are needed (a launch less:
+// clearing and 128-token blocks took 4.6 + 6.8 us at 1,024 tokens).
+// Short blocks where there would be too few to fill the chip, longer ones where attn_vt_prep
+// would have many to read (42,196 tokens: 20.9 + 43.9 us in blocks of 128 against 25.3 + 47.6 in
+// blocks of 32).
+inline int amax_tokens(int N) { return N <= 8192 ? 32 : 128; }
 constexpr int kAmaxMaxHeads = 256;
 __global__ __launch_bounds__(256) void attn_v_amax(const VtParams p) {
   __shared__ uint32_t sm[kAmaxMaxHeads * 10];
   const int s = blockIdx.x / p.tiles, b = blockIdx.x - s * p.tiles;   // tiles: blocks per segment
   const int c0 = p.cu[s], L = p.cu[s + 1] - c0;
-  const int t0 = b * kAmaxTok;
+  const int t0 = b * p.tok;
   if (t0 >= L) return;   // the whole workgroup leaves together
-  const int nt = min(kAmaxTok, L - t0);
+  const int nt = min(p.tok, L - t0);
   const int slots = p.H * 10;
   const uint4* base = reinterpret_cast<const uint4*>(p.v + static_cast<long long>(c0 + t0) * p.H * 80);
   for (int slot = threadIdx.x; slot < slots; slot += 256) {
     uint32_t m = 0u;
-#pragma unroll 8
-    for (int r = 0; r < nt; ++r) {
-      const uint4 u = base[static_cast<long long>(r) * slots + slot];
-      const uint32_t w4[4] = {u.x, u.y, u.z, u.w};
+    for (int r0 = 0; r0 < nt; r0 += 8) {   // eight loads in flight; rows past the last repeat it
+      uint4 u[8];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) m = max(m, max(w4[e] & 0x7fffu, (w4[e] >> 16) & 0x7fffu));
+      for (int r = 0; r < 8; ++r) u[r] = base[static_cast<long long>(min(r0 + r, nt - 1)) * slots + slot];
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {
+        const uint32_t w4[4] = {u[r].x, u[r].y, u[r].z, u[r].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) m = max(m, max(w4[e] & 0x7fffu, (w4[e] >> 16) & 0x7fffu));
+      }
     }
     sm[slot] = m;
   }
   __syncthreads();
+  const long long e = amax_entry(p, c0, s, b) * p.part_i;
   for (int h = threadIdx.x; h < p.H; h += 256) {
     uint32_t m = 0u;
 #pragma unroll
     for (int c = 0; c < 10; ++c) m = max(m, sm[h * 10 + c]);
-    if (m != 0u) atomicMax(&p.amax[s * p.H + h], m);
+    p.part[e + h * p.part_h] = m;
   }
 }
 
@@ -674,13 +687,34 @@ __global__ __launch_bounds__(256) void attn_vt_prep(const VtParams p) {
   const int width = vt_start(p.cu[s + 1], s + 1) - col0;
   if (64 * t >= width) return;   // the whole workgroup leaves together
   const int tid = threadIdx.x;
-  const int shift = vt_shift(p.amax[s * p.H + h]);
-  for (int c = tid; c < 64 * 10; c += 256) {
-    const int key = c / 10, ch = c - (c / 10) * 10;
+  // the tile's V rows, 16-byte chunks, requested before the maxima
+  constexpr int kPer = (64 * 10 + 255) / 256;
+  uint4 u[kPer];
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    const int c = tid + 256 * i, key = c / 10, ch = c - (c / 10) * 10;
     const int j = 64 * t + key;
-    uint4 u = make_uint4(0u, 0u, 0u, 0u);
-    if (j < L) u = *reinterpret_cast<const uint4*>(p.v + (static_cast<long long>(c0 + j) * p.H + h) * 80 + ch * 8);
-    const uint32_t w4[4] = {u.x, u.y, u.z, u.w};
+    u[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (c < 64 * 10 && j < L)
+      u[i] = *reinterpret_cast<const uint4*>(p.v + (static_cast<long long>(c0 + j) * p.H + h) * 80 + ch * 8);
+  }
+  // the segment's largest |v| of this head, over its token blocks
+  __shared__ uint32_t wmax[4];
+  uint32_t am = 0u;
+  for (int b = tid; b < (L + p.tok - 1) / p.tok; b += 256)
+    am = max(am, p.part[amax_entry(p, c0, s, b) * p.part_i + h * p.part_h]);
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) am = max(am, static_cast<uint32_t>(__shfl_xor(am, o, 64)));
+  if ((tid & 63) == 0) wmax[tid >> 6] = am;
+  __syncthreads();
+  am = max(max(wmax[0], wmax[1]), max(wmax[2], wmax[3]));
+  if (t == 0 && tid == 0) p.amax[s * p.H + h] = am;   // for the output's scale
+  const int shift = vt_shift(am);
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    const int c = tid + 256 * i, key = c / 10, ch = c - (c / 10) * 10;
+    if (c >= 64 * 10) break;
+    const uint32_t w4[4] = {u[i].x, u[i].y, u[i].z, u[i].w};
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const uint32_t pk = pack_f16x2(__builtin_amdgcn_ldexpf(__uint_as_float(w4[e] << 16), shift),
@@ -710,6 +744,7 @@ __device__ __forceinline__ void phase_sync() {
 constexpr int kRotWaves = 12;
 constexpr int kRotThreads = 64 * kRotWaves;
 constexpr int kRotBM = 32 * kRotWaves;                // query rows per workgroup
+constexpr int kRotSplitBM = 32 * kRotWaves / 3;       // the same when the groups split the keys
 constexpr int kVtStride = kBN + 8;                    // LDS row stride of a V^T tile (elements)
 constexpr int kVtChunks = kVtRows * (kVtStride / 8);  // 16-byte DMA chunks per V^T tile
 constexpr int kVtInst = (kVtChunks + 63) / 64;        // wave-wide DMA loads per V^T tile
@@ -720,12 +755,16 @@ constexpr float kP16Shift = 7.0f;                     // log2 of P's scale facto
 // Row order of K in S^T = K Q^T: bits 2 and 3 of the row index swapped (an involution).
 __device__ __forceinline__ int swap_bits23(int r) { return (r & ~12) | ((r & 4) << 1) | ((r & 8) >> 1); }
 
-template <int D>
+// With SPLIT (few rows: see rot_split) the three groups work on the same 128 query rows and take
+// every third key tile each, with K and V^T buffers of their own; their partial O^T and row sums
+// are added at the end, in group order, relative to the largest of their row maxima.
+template <int D, bool SPLIT>
 __global__ __launch_bounds__(kRotThreads, 1) void attn_fwd_rot(const FwdParams p) {
   static_assert(D == 80, "the rotation kernel is laid out for head dim 80");
   using C = FwdCfg<D>;
-  __shared__ __align__(16) uint16_t Ks[3][kBN * C::KS];
-  __shared__ __align__(16) uint16_t Vt[4][C::DV * kVtStride];   // fp16 V^T tiles (rows 81.. unused)
+  constexpr int kKT = kBN * C::KS, kVT = C::DV * kVtStride;   // elements of a K and a V^T tile
+  // K and fp16 V^T tiles: three and four shared by all groups, or two and two per group
+  __shared__ __align__(16) uint16_t lds[SPLIT ? 3 * (2 * kKT + 2 * kVT) : 3 * kKT + 4 * kVT];
 
   const int lb = remap_block_id(blockIdx.x, gridDim.x);
   const int per_head = p.nseg * p.nqt;
@@ -735,13 +774,15 @@ __global__ __launch_bounds__(kRotThreads, 1) void attn_fwd_rot(const FwdParams p
   const int qt = rem - seg * p.nqt;
   const int s0 = p.cu[seg];
   const int L = p.cu[seg + 1] - s0;
-  const int q0 = qt * kRotBM;
+  const int q0 = qt * (SPLIT ? kRotSplitBM : kRotBM);
   if (q0 >= L) return;   // the whole workgroup leaves together
   const int kvh = h / p.group;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int grp = w >> 2, wl = w & 3;
   const int lane = tid & 63, g = lane >> 5, c32 = lane & 31;
-  const int qrow = q0 + w * 32 + c32;
+  const int wrow = (SPLIT ? wl : w) * 32;   // the wave's first query row in the workgroup
+  const int qrow = q0 + wrow + c32;
+  const int kbase = SPLIT ? grp * (2 * kKT + 2 * kVT) : 0, vbase = kbase + (SPLIT ? 2 : 3) * kKT;
   const int qstride = p.Hq * D;
   const int kvstride = p.Hkv * D;
 
@@ -776,26 +817,39 @@ __global__ __launch_bounds__(kRotThreads, 1) void attn_fwd_rot(const FwdParams p
                    : kOutOfRange;
   });
   const unsigned tile_bytes = static_cast<unsigned>(kBN * kvstride) * 2u;
-  const unsigned ks_lds = lds_u32(&Ks[0][0]), vt_lds = lds_u32(&Vt[0][0]);
+  const unsigned ks_lds = lds_u32(lds + kbase), vt_lds = lds_u32(lds + vbase);
   // tile t of K and V^T: the resources move to the tile (scalar work), the lane offsets stay
+  auto dma_k = [&](i32x4 r, int kbuf) __attribute__((always_inline)) {
+    static_for<0, C::KPW>([&](auto I) __attribute__((always_inline)) {
+      if (wl + 4 * I < C::KINST) dma16(r, ks_lds + (kbuf * kKT + (wl + 4 * I) * 512) * 2, koff[I]);
+    });
+  };
+  auto dma_v = [&](i32x4 r, int vbuf) __attribute__((always_inline)) {
+    static_for<0, kVtPW>([&](auto I) __attribute__((always_inline)) {
+      if (wl + 4 * I < kVtInst) dma16(r, vt_lds + (vbuf * kVT + (wl + 4 * I) * 512) * 2, vtoff[I]);
+    });
+  };
+  auto load_k = [&](int t, int kbuf) __attribute__((always_inline)) {
+    dma_k(rsrc_advance(rk, static_cast<unsigned>(t) * tile_bytes), kbuf);
+  };
+  auto load_v = [&](int t, int vbuf) __attribute__((always_inline)) {
+    dma_v(rsrc_advance(rvt, static_cast<unsigned>(t) * (kBN * 2)), vbuf);
+  };
   auto load_kv = [&](int t, int kbuf, int vbuf) __attribute__((always_inline)) {
     const i32x4 rkt = rsrc_advance(rk, static_cast<unsigned>(t) * tile_bytes);
     const i32x4 rvtt = rsrc_advance(rvt, static_cast<unsigned>(t) * (kBN * 2));
-    static_for<0, C::KPW>([&](auto I) __attribute__((always_inline)) {
-      if (wl + 4 * I < C::KINST)
-        dma16(rkt, ks_lds + (kbuf * kBN * C::KS + (wl + 4 * I) * 512) * 2, koff[I]);
-    });
-    static_for<0, kVtPW>([&](auto I) __attribute__((always_inline)) {
-      if (wl + 4 * I < kVtInst)
-        dma16(rvtt, vt_lds + (vbuf * C::DV * kVtStride + (wl + 4 * I) * 512) * 2, vtoff[I]);
-    });
+    dma_k(rkt, kbuf);
+    dma_v(rvtt, vbuf);
   };
 
+  // loaded once, before the loop (else the compiler waits for it in every tile)
+  float scale_log2 = p.scale_log2;
+  asm volatile("" : "+s"(scale_log2));
   f32x16 s[2];
   const int krow = swap_bits23(c32);
   // half st of S^T(tile in K buffer kb): key rows 32 st + swap_bits23(0..31)
   auto qk_half = [&](int kb, int st) __attribute__((always_inline)) {
-    const uint16_t* kp = &Ks[kb][(st * 32 + krow) * C::KS + g * 8];
+    const uint16_t* kp = lds + kbase + kb * kKT + (st * 32 + krow) * C::KS + g * 8;
     bf16x8 kf[C::KC];
 #pragma unroll
     for (int c = 0; c < C::KC; ++c) kf[c] = *reinterpret_cast<const bf16x8*>(kp + c * 16);
@@ -816,8 +870,8 @@ __global__ __launch_bounds__(kRotThreads, 1) void attn_fwd_rot(const FwdParams p
   auto exps = [&](auto R0, auto R1) __attribute__((always_inline)) {
     static_for<decltype(R0)::value / 2, decltype(R1)::value / 2>([&](auto J) __attribute__((always_inline)) {
       constexpr int r = 2 * decltype(J)::value, st = r >> 4, rr = r & 15;
-      const float e0 = fast_exp2(s[st][rr] * p.scale_log2 - m_off);
-      const float e1 = fast_exp2(s[st][rr + 1] * p.scale_log2 - m_off);
+      const float e0 = fast_exp2(s[st][rr] * scale_log2 - m_off);
+      const float e1 = fast_exp2(s[st][rr + 1] * scale_log2 - m_off);
       pw[st][rr >> 3][(rr & 7) >> 1] = pack_f16x2(e0, e1);
       // pin the results to this phase: left alone, the compiler sinks them past the barrier
       asm volatile("" : "+v"(pw[st][rr >> 3][(rr & 7) >> 1]));
@@ -850,7 +904,7 @@ __global__ __launch_bounds__(kRotThreads, 1) void attn_fwd_rot(const FwdParams p
     float mx = vmax3(vmax3(m2a, m2b, m2c), m1[9], m1[9]);
     {   // the two half-waves hold the same query rows: exchange halves without an LDS round trip
       const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-      mx = vmax3(__uint_as_float(sw[0]), __uint_as_float(sw[1]), __uint_as_float(sw[1])) * p.scale_log2;
+      mx = vmax3(__uint_as_float(sw[0]), __uint_as_float(sw[1]), __uint_as_float(sw[1])) * scale_log2;
     }
     if (__builtin_amdgcn_ballot_w64(mx > m_thresh) != 0ull) {
       const float m_new = fmaxf(m_used, mx);
@@ -870,7 +924,7 @@ __global__ __launch_bounds__(kRotThreads, 1) void attn_fwd_rot(const FwdParams p
   // fragments are read first and the V^T fragments while the S^T MFMAs run (the two halves'
   // chains interleaved), a few reads ahead of their MFMAs throughout.
   auto phase_b = [&](int kb, int vb) __attribute__((always_inline)) {
-    const uint16_t* kp = &Ks[kb][krow * C::KS + g * 8];
+    const uint16_t* kp = lds + kbase + kb * kKT + krow * C::KS + g * 8;
     bf16x8 k0[C::KC], k1[C::KC];
 #pragma unroll
     for (int c = 0; c < C::KC; ++c) {
@@ -878,7 +932,7 @@ __global__ __launch_bounds__(kRotThreads, 1) void attn_fwd_rot(const FwdParams p
       k1[c] = *reinterpret_cast<const bf16x8*>(kp + 32 * C::KS + c * 16);
     }
     uint4 va[12];
-    const uint16_t* vp = &Vt[vb][c32 * kVtStride + g * 8];
+    const uint16_t* vp = lds + vbase + vb * kVT + c32 * kVtStride + g * 8;
 #pragma unroll
     for (int f = 0; f < 12; ++f) {
       const int st = f / 6, hh = (f / 3) & 1, t2 = f % 3;
@@ -920,43 +974,105 @@ __global__ __launch_bounds__(kRotThreads, 1) void attn_fwd_rot(const FwdParams p
 #pragma unroll
         for (int t2 = 0; t2 < C::NT; ++t2) {
           const uint4 a = *reinterpret_cast<const uint4*>(
-              &Vt[vb][(t2 * 32 + c32) * kVtStride + st * 32 + hh * 16 + g * 8]);
+              lds + vbase + vb * kVT + (t2 * 32 + c32) * kVtStride + st * 32 + hh * 16 + g * 8);
           const uint4 bp = make_uint4(pw[st][hh][0], pw[st][hh][1], pw[st][hh][2], pw[st][hh][3]);
           oacc[t2] = mfma_f16(as_f16x8(a), as_f16x8(bp), oacc[t2]);
         }
   };
 
   const int ntiles = (L + kBN - 1) / kBN;
-  if (grp == 0) {
-    load_kv(0, 0, 0);
-    if (ntiles > 1) load_kv(1, 1, 1);
+  if constexpr (SPLIT) {
+    // group g takes the tiles g, g + 3, ...; K(i + 2) and V(i + 1) of a group's sequence are
+    // requested in its phase A2 of i, awaited at the end of A1 of i + 1
+    const int nit = (ntiles + 2) / 3;
+    if (grp < ntiles) { load_k(grp, 0); load_v(grp, 0); }
+    if (grp + 3 < ntiles) load_k(grp + 3, 1);
     wait_vmem();
-  }
-  phase_sync();
-  qk_half(0, 0);
-  qk_half(0, 1);
-  for (int i = 0; i < grp; ++i) phase_sync();   // group g runs g slots behind
-  int t = 0, kb = 0;                            // kb = t % 3
-  for (; t + 1 < ntiles; ++t) {
-    const int kb1 = (kb == 2) ? 0 : kb + 1, kb2 = (kb1 == 2) ? 0 : kb1 + 1;
+    phase_sync();
+    if (grp < ntiles) {
+      qk_half(0, 0);
+      qk_half(0, 1);
+    }
+    for (int i = 0; i < grp; ++i) phase_sync();
+#pragma unroll 1
+    for (int i = 0; i < nit; ++i) {
+      const int t = 3 * i + grp;
+      const bool act = t < ntiles, next = t + 3 < ntiles;   // wave-uniform
+      if (act) phase_a1(t * kBN);
+      wait_vmem();
+      phase_sync();
+      if (act) exps(std::integral_constant<int, kA1Vals>{}, std::integral_constant<int, 32>{});
+      if (t + 6 < ntiles) load_k(t + 6, i & 1);
+      if (next) load_v(t + 3, (i + 1) & 1);
+      phase_sync();
+      // past the group's last tile the S^T of whatever the K buffer holds goes unused
+      if (act) phase_b((i + 1) & 1, i & 1);
+      phase_sync();
+    }
+  } else {
+    if (grp == 0) {
+      load_kv(0, 0, 0);
+      if (ntiles > 1) load_kv(1, 1, 1);
+      wait_vmem();
+    }
+    phase_sync();
+    qk_half(0, 0);
+    qk_half(0, 1);
+    for (int i = 0; i < grp; ++i) phase_sync();   // group g runs g slots behind
+    int t = 0, kb = 0;                            // kb = t % 3
+    for (; t + 1 < ntiles; ++t) {
+      const int kb1 = (kb == 2) ? 0 : kb + 1, kb2 = (kb1 == 2) ? 0 : kb1 + 1;
+      phase_a1(t * kBN);
+      if (grp == 0) wait_vmem();   // K(t+1) and V^T(t+1), issued during phase A2 of tile t-1
+      phase_sync();
+      exps(std::integral_constant<int, kA1Vals>{}, std::integral_constant<int, 32>{});
+      if (grp == 0 && t + 2 < ntiles) load_kv(t + 2, kb2, (t + 2) & 3);
+      phase_sync();
+      phase_b(kb1, t & 3);
+      phase_sync();
+      kb = kb1;
+    }
+    // last tile: nothing left to load or to multiply ahead
     phase_a1(t * kBN);
-    if (grp == 0) wait_vmem();   // K(t+1) and V^T(t+1), issued during phase A2 of tile t-1
     phase_sync();
     exps(std::integral_constant<int, kA1Vals>{}, std::integral_constant<int, 32>{});
-    if (grp == 0 && t + 2 < ntiles) load_kv(t + 2, kb2, (t + 2) & 3);
     phase_sync();
-    phase_b(kb1, t & 3);
+    pv(t & 3);
     phase_sync();
-    kb = kb1;
   }
-  // last tile: nothing left to load or to multiply ahead
-  phase_a1(t * kBN);
-  phase_sync();
-  exps(std::integral_constant<int, kA1Vals>{}, std::integral_constant<int, 32>{});
-  phase_sync();
-  pv(t & 3);
-  phase_sync();
   for (int i = grp; i < 2; ++i) phase_sync();   // equal barrier counts in every group
+
+  if constexpr (SPLIT) {
+    // The groups' partial results of the same rows: all brought to the largest of the three
+    // maxima, then added by group 0 in group order.  Every wave is past its last tile reads.
+    float* mx = reinterpret_cast<float*>(lds);            // [3][128]
+    float* part = mx + 3 * kRotSplitBM;                   // [2][4 waves][NT * 16][64 lanes]
+    static_assert((3 * kRotSplitBM + 2 * 4 * C::NT * 16 * 64) * 4 <= 3 * (2 * kKT + 2 * kVT) * 2, "partials do not fit");
+    if (g == 0) mx[grp * kRotSplitBM + wl * 32 + c32] = m_used;
+    __syncthreads();
+    const float* mr = mx + wl * 32 + c32;
+    const float m_all = fmaxf(fmaxf(mr[0], mr[kRotSplitBM]), mr[2 * kRotSplitBM]);
+    const float f = fast_exp2(m_used - m_all);            // 0 for a group without tiles
+    m_off = m_all - kP16Shift;
+#pragma unroll
+    for (int t2 = 0; t2 < C::NT; ++t2)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        oacc[t2][r] *= f;
+        if (grp > 0) part[(((grp - 1) * 4 + wl) * C::NT * 16 + t2 * 16 + r) * 64 + lane] = oacc[t2][r];
+      }
+    __syncthreads();
+    if (grp == 0) {
+#pragma unroll
+      for (int t2 = 0; t2 < C::NT; ++t2)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          oacc[t2][r] = oacc[t2][r] + part[(wl * C::NT * 16 + t2 * 16 + r) * 64 + lane] +
+                        part[((4 + wl) * C::NT * 16 + t2 * 16 + r) * 64 + lane];
+    }
+    __syncthreads();
+    if (grp > 0) return;   // group 0's four waves write the rows
+  }
 
   // row 80 of O^T (register 8 of block 2 in the lanes of half 0) is the row sum of P; the
   // V^T tiles carry V scaled by 2^shift, undone here (exact)
@@ -965,13 +1081,12 @@ __global__ __launch_bounds__(kRotThreads, 1) void attn_fwd_rot(const FwdParams p
   const int unshift = -vt_shift(p.vt_amax[seg * p.Hkv + kvh]);
   if (qrow < L && g == 0 && p.lse)
     p.lse[static_cast<long long>(h) * p.Ntot + s0 + qrow] = (m_off + __builtin_amdgcn_logf(l)) * kLn2;
-  // O through each wave's own 32 rows: waves 0-5 in the V^T buffers, 6-11 in the K buffers
-  // (every wave is past its last tile reads: the barriers above)
-  static_assert(6 * 32 * (D + 8) <= 4 * C::DV * kVtStride && 6 * 32 * (D + 8) <= 3 * kBN * C::KS,
-                "staged O does not fit the tile buffers");
-  uint16_t* stage = (w < 6) ? &Vt[0][0] + w * 32 * (D + 8) : &Ks[0][0] + (w - 6) * 32 * (D + 8);
-  store_o_staged<D>(oacc, inv_l, unshift, stage,
-                    make_rsrc(p.o + static_cast<long long>(s0) * qstride + h * D, seg_bytes_q), q0 + w * 32, qstride);
+  // O through each wave's own 32 rows (every wave is past its last tile reads: the barriers
+  // above; the rows are the wave's own, so no barrier of the workgroup is needed)
+  static_assert(kRotWaves * 32 * (D + 8) <= 3 * kKT + 4 * kVT, "staged O does not fit the tile buffers");
+  store_o_staged<D, C::NT, false>(oacc, inv_l, unshift, lds + w * 32 * (D + 8),
+                                  make_rsrc(p.o + static_cast<long long>(s0) * qstride + h * D, seg_bytes_q), q0 + wrow,
+                                  qstride);
 }
 
 // ---------------------------------------------------------------- windows, fused mass
@@ -1185,12 +1300,12 @@ struct MassParams {
 constexpr int kMassKeys = 256;   // keys per workgroup (4 waves x 64)
 constexpr int kMassQ = 64;       // query rows per tile (two MFMA column blocks of 32)
 
-template <int D>
+template <int D, int QROWS = kMassQ>
 struct MassCfg {
   static constexpr int KC = D / 16;
   static constexpr int QROW = D / 8 + 1;                     // 16-byte chunks per Q row (odd)
   static constexpr int QS = QROW * 8;                        // LDS row stride (elements)
-  static constexpr int QINST = (kMassQ * QROW + 63) / 64;    // wave-wide DMA loads per Q tile
+  static constexpr int QINST = (QROWS * QROW + 63) / 64;     // wave-wide DMA loads per Q tile
   static constexpr int QBUF = QINST * 512;                   // elements per buffer (incl. overhang)
   static constexpr int QPW = (QINST + 3) / 4;
 };
@@ -1200,11 +1315,19 @@ struct MassCfg {
 // computes S^T(t) = K Q(t)^T on the MFMA pipe, then on the VALU
 // P = exp2(S * scale * log2 e - LSE * log2 e), the exact normalised probability, summed per
 // key in fp32 (each lane owns 16 keys of one query column).
-template <int D, bool CAUSAL>
-__global__ __launch_bounds__(kThreads, (D == 80 && !CAUSAL) ? 3 : 2) void attn_mass(const MassParams p) {
-  using C = MassCfg<D>;
-  __shared__ __align__(16) uint16_t Qs[3][C::QBUF];
-  __shared__ __align__(16) float Ls[3][kMassQ];   // LSE of each Q tile's rows (natural log)
+//
+// With QSPLIT (few keys: see launch_mass) the four waves hold the same 64 keys and wave w streams
+// the 32-row query tiles w, w + 4, ... through a ring of its own, without barriers; the four sums
+// per key are added at the end, in wave order.
+template <int D, bool CAUSAL, bool QSPLIT>
+__global__ __launch_bounds__(kThreads, QSPLIT ? 2 : (D == 80 && !CAUSAL) ? 3 : 2) void attn_mass(const MassParams p) {
+  constexpr int kQ = QSPLIT ? kMassQ / 2 : kMassQ;             // query rows per tile
+  using C = MassCfg<D, kQ>;
+  static_assert(!QSPLIT || (D == 80 && !CAUSAL), "the query split is built on the block pipeline");
+  constexpr int kKeys = QSPLIT ? kMassKeys / 4 : kMassKeys;   // keys per workgroup
+  constexpr int kRings = QSPLIT ? 4 : 1;                      // rings of query tiles: one per wave or one for all
+  __shared__ __align__(16) uint16_t Qsm[kRings][3][C::QBUF];
+  __shared__ __align__(16) float Lsm[kRings][3][kMassQ];   // LSE of each Q tile's rows (natural log)
 
   const int lb = remap_block_id(blockIdx.x, gridDim.x);
   const int per_head = p.nseg * p.nkt;
@@ -1217,8 +1340,8 @@ __global__ __launch_bounds__(kThreads, (D == 80 && !CAUSAL) ? 3 : 2) void attn_m
   // keys [kst, kst + klen) of the segment receive mass
   const int kst = p.key_start ? p.key_start[seg] : 0;
   const int klen = p.key_len ? p.key_len[seg] : L - kst;
-  if (kt * kMassKeys >= klen) return;
-  const int k0 = kst + kt * kMassKeys;
+  if (kt * kKeys >= klen) return;   // the whole workgroup leaves together
+  const int k0 = kst + kt * kKeys;
   const int kend = kst + klen;
   const int qs = p.q_start ? p.q_start[seg] : 0;
   const int ql = p.q_len ? p.q_len[seg] : L;
@@ -1228,7 +1351,12 @@ __global__ __launch_bounds__(kThreads, (D == 80 && !CAUSAL) ? 3 : 2) void attn_m
   const int lane = tid & 63, g = lane >> 5, c32 = lane & 31;
   const int qstride = p.Hq * D;
   const int kvstride = p.Hkv * D;
-  const int kw0 = k0 + w * 64;   // first key of this wave
+  const int kw0 = k0 + (QSPLIT ? 0 : w * 64);   // first key of this wave
+  auto& Qs = Qsm[QSPLIT ? w : 0];
+  auto& Ls = Lsm[QSPLIT ? w : 0];
+  // a ring's tiles are loaded by its waves: one wave or four
+  constexpr int kLoaders = QSPLIT ? 1 : 4, kQPW = (C::QINST + kLoaders - 1) / kLoaders;
+  const int wq = QSPLIT ? 0 : w;
 
   // K fragments (A operand of S^T = K Q^T) for the wave's two 32-key sets; keys past the
   // receiving range load as zeros (their mass is never written)
@@ -1247,31 +1375,32 @@ __global__ __launch_bounds__(kThreads, (D == 80 && !CAUSAL) ? 3 : 2) void attn_m
                                 ql > 0 ? static_cast<unsigned>((ql - 1) * qstride + D) * 2u : 0u);
   const auto rl = make_dma_rsrc(p.lse + static_cast<long long>(h) * p.Ntot + s0 + qs,
                                 static_cast<unsigned>(ql) * 4u);
-  unsigned qoff[C::QPW];
-  static_for<0, C::QPW>([&](auto I) __attribute__((always_inline)) {
-    const int c = (w + 4 * I) * 64 + lane;
+  unsigned qoff[kQPW];
+  static_for<0, kQPW>([&](auto I) __attribute__((always_inline)) {
+    const int c = (wq + kLoaders * I) * 64 + lane;
     const int r = c / C::QROW, cc = c % C::QROW;
-    qoff[I] = (cc < D / 8 && r < kMassQ && w + 4 * I < C::QINST)
+    qoff[I] = (cc < D / 8 && r < kQ && wq + kLoaders * I < C::QINST)
                   ? static_cast<unsigned>(r * qstride + cc * 8) * 2u : kOutOfRange;
   });
-  const unsigned qtile_bytes = static_cast<unsigned>(kMassQ * qstride) * 2u;
+  const unsigned qtile_bytes = static_cast<unsigned>(kQ * qstride) * 2u;
   const unsigned qs_lds = lds_u32(&Qs[0][0]);
   // The LSE rows of a tile come with its Q rows, by DMA from the wave with the fewest Q chunks.
-  constexpr int kLseWave = C::QINST % 4;
+  constexpr int kLseWave = QSPLIT ? 0 : C::QINST % 4;
   const unsigned ls_lds = lds_u32(&Ls[0][0]);
   auto load_q = [&](int t, int buf) __attribute__((always_inline)) {
-    static_for<0, C::QPW>([&](auto I) __attribute__((always_inline)) {
-      if (w + 4 * I < C::QINST) dma16(rq, qs_lds + (buf * C::QBUF + (w + 4 * I) * 512) * 2, qoff[I] + t * qtile_bytes);
+    static_for<0, kQPW>([&](auto I) __attribute__((always_inline)) {
+      if (wq + kLoaders * I < C::QINST)
+        dma16(rq, qs_lds + (buf * C::QBUF + (wq + kLoaders * I) * 512) * 2, qoff[I] + t * qtile_bytes);
     });
-    if (w == kLseWave) dma4(rl, ls_lds + buf * kMassQ * 4, static_cast<unsigned>(t * kMassQ + lane) * 4u);
+    if (wq == kLseWave) dma4(rl, ls_lds + buf * kMassQ * 4, static_cast<unsigned>(t * kQ + lane) * 4u);
   };
   // DMA instructions this wave issues per tile
-  int dma_per_tile = (w == kLseWave) ? 1 : 0;
-  static_for<0, C::QPW>([&](auto I) __attribute__((always_inline)) { dma_per_tile += (w + 4 * I < C::QINST) ? 1 : 0; });
+  int dma_per_tile = (wq == kLseWave) ? 1 : 0;
+  static_for<0, kQPW>([&](auto I) __attribute__((always_inline)) { dma_per_tile += (wq + kLoaders * I < C::QINST) ? 1 : 0; });
   // LSE of this lane's query row of the tile in buffer buf (log2 units); rows past the range
   // get +inf -> P = 0
   auto load_lse2 = [&](int t, int buf, int u) __attribute__((always_inline)) {
-    const int r = t * kMassQ + u * 32 + c32;
+    const int r = t * kQ + u * 32 + c32;
     const float v = Ls[buf][u * 32 + c32];
     return (r < ql) ? v * kLog2e : INFINITY;
   };
@@ -1314,7 +1443,7 @@ __global__ __launch_bounds__(kThreads, (D == 80 && !CAUSAL) ? 3 : 2) void attn_m
 
   // Three query-tile buffers: Q(t+2) and its LSE rows are loaded while Q(t) is read, into the
   // buffer of Q(t-1) that every wave left behind at this iteration's barrier.
-  const int ntiles = (ql + kMassQ - 1) / kMassQ;
+  const int ntiles = (ql + kQ - 1) / kQ;
   if constexpr (D == 80 && !CAUSAL) {
     // Pipelined within the wave, one 32-key x 32-row block of S^T at a time: the tile's blocks
     // (half u, key set ks) go in the order (0,0) (0,1) (1,0) (1,1), and the MFMAs of each block
@@ -1344,17 +1473,43 @@ __global__ __launch_bounds__(kThreads, (D == 80 && !CAUSAL) ? 3 : 2) void attn_m
         __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);
       });
     };
-    if (ntiles > 0) {
-      load_q(0, 0);
-      if (ntiles > 1) load_q(1, 1);
+    // QSPLIT: wave w takes the tiles w, w + 4, ... through a ring of its own, without barriers
+    const int n_my = QSPLIT ? (ntiles - w + 3) / 4 : ntiles;
+    auto tile_of = [&](int i) __attribute__((always_inline)) { return QSPLIT ? w + 4 * i : i; };
+    if (n_my > 0) {
+      load_q(tile_of(0), 0);
+      if (n_my > 1) load_q(tile_of(1), 1);
       f32x16 s3 = f32x16{};    // block (1,1) of the previous tile
       float l2p = INFINITY;    // its rows' LSE: +inf makes the first iteration's sums add zeros
       // tile t in buffer buf = t % 3; only the LAST tile can hold rows past the querying range
       // (ntiles = ceil(ql / 64)), so only it masks them
-      auto tile = [&](int buf, auto LAST, int t) __attribute__((always_inline)) {
+      auto tile = [&](int buf, auto LAST, int i) __attribute__((always_inline)) {
         constexpr bool last = decltype(LAST)::value;
-        wait_vmem_upto(last ? 0 : dma_per_tile);
-        __syncthreads();
+        const int t = tile_of(i);
+        if constexpr (QSPLIT) {
+          static_assert(C::QINST + 1 == 7 || !QSPLIT, "the wait below counts a tile's DMAs");
+          if constexpr (last) wait_vmem(); else asm volatile("s_waitcnt vmcnt(7)" ::: "memory");
+        } else {
+          wait_vmem_upto(last ? 0 : dma_per_tile);
+          __syncthreads();
+        }
+        if constexpr (QSPLIT) {   // the blocks of one 32-row half
+          const float l2 = last ? load_lse2(t, buf, 0) : Ls[buf][c32] * kLog2e;
+          if (i + 2 < n_my) load_q(tile_of(i + 2), (buf == 0) ? 2 : buf - 1);
+          bf16x8 qa[C::KC];
+          q_frags(buf, 0, qa);
+          __builtin_amdgcn_sched_barrier(0);
+          const f32x16 s0 = chain(0, qa);
+          sums(s3, l2p, 1);
+          interleave();
+          __builtin_amdgcn_sched_barrier(0);
+          s3 = chain(1, qa);
+          sums(s0, l2, 0);
+          interleave();
+          __builtin_amdgcn_sched_barrier(0);
+          l2p = l2;
+          return;
+        }
         float l2a, l2b;
         if constexpr (last) {
           l2a = load_lse2(t, buf, 0);
@@ -1364,7 +1519,7 @@ __global__ __launch_bounds__(kThreads, (D == 80 && !CAUSAL) ? 3 : 2) void attn_m
           l2b = Ls[buf][32 + c32] * kLog2e;
         }
         const int buf2 = (buf == 0) ? 2 : buf - 1;   // (t + 2) % 3
-        if (t + 2 < ntiles) load_q(t + 2, buf2);
+        if (i + 2 < n_my) load_q(tile_of(i + 2), buf2);
         bf16x8 qa[C::KC], qc[C::KC];
         q_frags(buf, 0, qa);
         __builtin_amdgcn_sched_barrier(0);
@@ -1388,11 +1543,11 @@ __global__ __launch_bounds__(kThreads, (D == 80 && !CAUSAL) ? 3 : 2) void attn_m
         l2p = l2b;
       };
       int buf = 0;
-      for (int t = 0; t + 1 < ntiles; ++t) {
-        tile(buf, std::false_type{}, t);
+      for (int i = 0; i + 1 < n_my; ++i) {
+        tile(buf, std::false_type{}, i);
         buf = (buf == 2) ? 0 : buf + 1;
       }
-      tile(buf, std::true_type{}, ntiles - 1);
+      tile(buf, std::true_type{}, n_my - 1);
       sums(s3, l2p, 1);
     }
   } else if (ntiles > 0) {
@@ -1426,6 +1581,19 @@ __global__ __launch_bounds__(kThreads, (D == 80 && !CAUSAL) ? 3 : 2) void attn_m
       macc[ks][r] = x;
     }
   float* mrow = p.mass + static_cast<long long>(h) * p.mass_stride + moff;
+  if constexpr (QSPLIT) {
+    // the four waves' sums of the same 64 keys, added in wave order
+    __shared__ float part[4][64];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (c32 == r) part[w][ks * 32 + g * 4 + 8 * (r >> 2) + (r & 3)] = macc[ks][r];
+    __syncthreads();
+    if (w == 0 && kw0 + lane < kend)
+      mrow[kw0 + lane - kst] = ((part[0][lane] + part[1][lane]) + part[2][lane]) + part[3][lane];
+    return;
+  }
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
@@ -1441,9 +1609,43 @@ __global__ __launch_bounds__(kThreads, (D == 80 && !CAUSAL) ? 3 : 2) void attn_m
 // forward kernel; at head dim 128 its per-wave state would not fit in registers.
 constexpr int kRotMinSeg = 1024;
 
+// Upper bound of the blocks of `rows` rows in nseg segments of at most max_seglen, N rows in all
+// (the segments' lengths are on the device); exact for one segment.
+inline long long blocks_bound(int N, int nseg, int max_seglen, int rows) {
+  const long long a = static_cast<long long>(nseg) * ((max_seglen + rows - 1) / rows), b = static_cast<long long>(N) / rows + nseg;
+  return a < b ? a : b;
+}
+
+// The groups of the rotation kernel split the keys (128 rows per workgroup) when all such
+// workgroups fit the chip at once; else 384 rows per workgroup.  Forward of 1,024, 1,540 and 2,048
+// patches x 16 heads with its V^T preparation: 39.3, 53.2 and 61.9 us in 384 rows, 30.8, 40.1 and
+// 48.3 us with the keys split; 3,000 patches (1.5 rounds): 82.9 against 87.9; 42,196: 8,084 against
+// 9,328 (each K and V^T tile serves a third of the rows).
+inline bool rot_split(int N, int nseg, int max_seglen, int H) {
+  return blocks_bound(N, nseg, max_seglen, kRotSplitBM) * H <= 256;
+}
+
+template <int D>
+pace_status_t launch_mass(MassParams mp, int max_seglen, hipStream_t stream) {
+  if constexpr (D == 80) {
+    // With fewer workgroups of 256 keys than CUs, the waves of a workgroup take the same 64 keys
+    // and split the query rows: 1,024, 2,048 and 3,000 patches x 16 heads 19.7, 32.3 and 44.4 us
+    // in 256 keys, 11.1, 21.8 and 39.8 us split; 4,096 (256 workgroups) 58.6 against 65.3; 42,196:
+    // 4,972 against 5,909 (each query tile serves a quarter of the keys).
+    if (blocks_bound(mp.Ntot, mp.nseg, max_seglen, kMassKeys) * mp.Hq < 256) {
+      mp.nkt = (max_seglen + kMassKeys / 4 - 1) / (kMassKeys / 4);
+      hipLaunchKernelGGL((attn_mass<80, false, true>), dim3(mp.nkt * mp.nseg * mp.Hq), dim3(kThreads), 0, stream, mp);
+      return check_launch("attn_mass");
+    }
+  }
+  mp.nkt = (max_seglen + kMassKeys - 1) / kMassKeys;
+  hipLaunchKernelGGL((attn_mass<D, false, false>), dim3(mp.nkt * mp.nseg * mp.Hq), dim3(kThreads), 0, stream, mp);
+  return check_launch("attn_mass");
+}
+
 template <int D>
 pace_status_t launch_attention(FwdParams fp, bool causal, int max_seglen, const MassParams* mp,
-                               int nmass, hipStream_t stream) {
+                               int nmass, void* scratch, hipStream_t stream) {
   if (!causal && mp != nullptr && nmass > 0 && max_seglen <= kWinMax && mp->mass_stride == fp.Ntot &&
       mp->key_start == nullptr && mp->key_len == nullptr && mp->q_start == nullptr && mp->q_len == nullptr &&
       mp->mass_off == nullptr) {
@@ -1460,27 +1662,40 @@ pace_status_t launch_attention(FwdParams fp, bool causal, int max_seglen, const 
     vp.v = fp.v; vp.vt = const_cast<uint16_t*>(fp.vt); vp.amax = const_cast<uint32_t*>(fp.vt_amax);
     vp.cu = fp.cu; vp.H = fp.Hkv; vp.cols = fp.vt_cols;
     vp.tiles = (max_seglen + 128 + kBN - 1) / kBN;   // a segment owns at most L + 127 columns
-    const int namax = fp.nseg * fp.Hkv;
-    hipLaunchKernelGGL(attn_vt_clear, dim3((namax + 255) / 256), dim3(256), 0, stream, vp.amax, namax);
+    // the blocks' maxima: [H][entries] in the LSE scratch (whose LSE is written later, if at all),
+    // or, if so many segments are empty that this does not fit, one block per segment straight
+    // into [nseg][H]
+    const int tok = amax_tokens(fp.Ntot);
+    const long long entries = fp.Ntot / tok + fp.nseg + 1ll;
+    vp.whole = entries > fp.Ntot;
+    vp.tok = vp.whole ? max_seglen : tok;
+    vp.part = vp.whole ? vp.amax : static_cast<uint32_t*>(scratch);
+    vp.part_i = vp.whole ? vp.H : 1;
+    vp.part_h = vp.whole ? 1 : entries;
     VtParams ap = vp;
-    ap.tiles = (max_seglen + kAmaxTok - 1) / kAmaxTok;
+    ap.tiles = (max_seglen + vp.tok - 1) / vp.tok;
     hipLaunchKernelGGL(attn_v_amax, dim3(ap.tiles * fp.nseg), dim3(256), 0, stream, ap);
     hipLaunchKernelGGL(attn_vt_prep, dim3(vp.tiles * fp.nseg, fp.Hkv), dim3(256), 0, stream, vp);
     pace_status_t st = check_launch("attn_vt_prep");
     if (st != PACE_OK) return st;
-    fp.nqt = (max_seglen + kRotBM - 1) / kRotBM;
-    hipLaunchKernelGGL((attn_fwd_rot<80>), dim3(fp.nqt * fp.nseg * fp.Hq), dim3(kRotThreads), 0, stream, fp);
+    if (rot_split(fp.Ntot, fp.nseg, max_seglen, fp.Hq)) {
+      fp.nqt = (max_seglen + kRotSplitBM - 1) / kRotSplitBM;
+      hipLaunchKernelGGL((attn_fwd_rot<80, true>), dim3(fp.nqt * fp.nseg * fp.Hq), dim3(kRotThreads), 0, stream, fp);
+    } else {
+      fp.nqt = (max_seglen + kRotBM - 1) / kRotBM;
+      hipLaunchKernelGGL((attn_fwd_rot<80, false>), dim3(fp.nqt * fp.nseg * fp.Hq), dim3(kRotThreads), 0, stream, fp);
+    }
   } else {
     fp.nqt = (max_seglen + kBM - 1) / kBM;
     hipLaunchKernelGGL((attn_fwd<D, false>), dim3(fp.nqt * fp.nseg * fp.Hq), dim3(kThreads), 0, stream, fp);
   }
   pace_status_t st = check_launch("attn_fwd");
   if (st != PACE_OK || mp == nullptr || nmass == 0) return st;
-  if (causal)
-    hipLaunchKernelGGL((attn_mass<D, true>), dim3(nmass), dim3(kThreads), 0, stream, *mp);
-  else
-    hipLaunchKernelGGL((attn_mass<D, false>), dim3(nmass), dim3(kThreads), 0, stream, *mp);
-  return check_launch("attn_mass");
+  if (causal) {
+    hipLaunchKernelGGL((attn_mass<D, true, false>), dim3(nmass), dim3(kThreads), 0, stream, *mp);
+    return check_launch("attn_mass");
+  }
+  return launch_mass<D>(*mp, max_seglen, stream);
 }
 
 }  // namespace
@@ -1558,8 +1773,8 @@ pace_status_t pace_vit_attention(const uint16_t* q, const uint16_t* k, const uin
   mp.nseg = nseg; mp.nkt = static_cast<int>(nkt);
   mp.scale_log2 = fp.scale_log2;
   const int nmass = mass ? static_cast<int>(nkt * nseg * H) : 0;
-  if (d == 80) return launch_attention<80>(fp, false, max_seglen, mass ? &mp : nullptr, nmass, stream);
-  return launch_attention<128>(fp, false, max_seglen, mass ? &mp : nullptr, nmass, stream);
+  if (d == 80) return launch_attention<80>(fp, false, max_seglen, mass ? &mp : nullptr, nmass, workspace, stream);
+  return launch_attention<128>(fp, false, max_seglen, mass ? &mp : nullptr, nmass, workspace, stream);
 }
 
 pace_status_t pace_vit_attention_mass(const uint16_t* q, const uint16_t* k, int N, int H, int d,
@@ -1585,12 +1800,7 @@ pace_status_t pace_vit_attention_mass(const uint16_t* q, const uint16_t* k, int 
   mp.Ntot = N; mp.Hq = H; mp.Hkv = H; mp.group = 1;
   mp.nseg = nseg; mp.nkt = static_cast<int>(nkt);
   mp.scale_log2 = scale * kLog2e;
-  const int nmass = static_cast<int>(nkt * nseg * H);
-  if (d == 80)
-    hipLaunchKernelGGL((attn_mass<80, false>), dim3(nmass), dim3(kThreads), 0, stream, mp);
-  else
-    hipLaunchKernelGGL((attn_mass<128, false>), dim3(nmass), dim3(kThreads), 0, stream, mp);
-  return check_launch("attn_mass");
+  return d == 80 ? launch_mass<80>(mp, max_seglen, stream) : launch_mass<128>(mp, max_seglen, stream);
 }
 
 pace_status_t pace_prefill_attention_with_mass(
@@ -1671,8 +1881,8 @@ pace_status_t pace_prefill_attention_with_mass(
   mp.scale_log2 = fp.scale_log2;
   // the mass kernel also runs when no row queries (it then writes zeros)
   const int nmass = (want_mass && nkt > 0) ? static_cast<int>(nkt * B * Hq) : 0;
-  if (d == 80) return launch_attention<80>(fp, true, max_seqlen, want_mass ? &mp : nullptr, nmass, stream);
-  return launch_attention<128>(fp, true, max_seqlen, want_mass ? &mp : nullptr, nmass, stream);
+  if (d == 80) return launch_attention<80>(fp, true, max_seqlen, want_mass ? &mp : nullptr, nmass, nullptr, stream);
+  return launch_attention<128>(fp, true, max_seqlen, want_mass ? &mp : nullptr, nmass, nullptr, stream);
 }
 
 }  // extern "C"

@@ -229,6 +229,30 @@ def _check_prefill(p):
     return mass, Mr
 
 
+@pytest.mark.parametrize("H,sizes", [(1, [1024]), (1, [1153, 1, 64, 65, 200]), (2, [1100, 0, 0, 129]), (16, [2048]),
+                                     (2, [16200]), (16, [2049]), (3, [1500] + [0] * 3000)])
+def test_vit_long_segment_splits_d80(H, sizes):
+    """Both forms of the long-segment forward (its groups split the rows or the keys) and of the
+    mass pass (its waves split the keys or the query rows), around the sizes where they change:
+    segments of one and two key tiles beside a long one (groups without a tile), no rows at all,
+    the largest grid of the split forms and the one above; more empty segments than tokens (the
+    maxima of V then come from one block per segment)."""
+    cu = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    q, k, v = _vit_case(131 + H, cu, H, 80)
+    if sizes[0] < 5000:
+        _check_vit(q, k, v, cu, 80)
+        return
+    # a long one: the rows at both ends of its blocks; every row of P sums to one
+    o, lse, mass = _run_vit(q, k, v, cu, sizes[0])
+    n = sizes[0]
+    rows = np.unique(np.clip(np.concatenate([np.arange(0, n, 128), np.arange(127, n, 128), [n - 1]]), 0, n - 1))
+    f = [wl.bf16_bits_to_f64(x) for x in (q, k, v)]
+    Or, Lr, _ = oatt.attention_segment(*f, False, 1 / math.sqrt(80), rows=rows, mass_rows=np.arange(0))
+    assert np.max(np.abs(o[rows] - Or)) <= O_TOL
+    assert np.max(np.abs(lse[:, rows] - Lr)) <= LSE_TOL
+    np.testing.assert_allclose(mass.sum(1), n, rtol=1e-4)
+
+
 def test_prefill_tiny_config():
     w = wl.make_workload(0)
     mass, Mr = _check_prefill(w.prefill)
