@@ -2,7 +2,7 @@
 // the bicubic resize by sqrt(r) per side (Appendix implementation details).
 //
 // Density, four launches (all HBM/L2-bound, fixed reduction orders -> deterministic):
-//   apc_patch_pass<0>  per patch-strip tile: ||f_i|| -> 1/||f_i|| (from exact integer sums of
+//   apc_patch_pass<0>  per patch-strip tile (256 or 1,024 threads): ||f_i|| -> 1/||f_i|| (from exact integer sums of
 //                      the bytes and their squares), and the tile's partial sum of
 //                      T_i = f_i/||f_i|| over its patches (one 588-vector per tile)
 //   apc_reduce_c       sum of the tile partials per component -> sum_i T_i
@@ -24,7 +24,6 @@ namespace pace {
 namespace {
 
 constexpr int kPatchesPerTile = 64;   // patches of one patch row per workgroup
-constexpr int kApcThreads = 256;      // 4 threads per patch for the norms
 constexpr int kMaxPatch = 16;
 
 struct DensityParams {
@@ -63,11 +62,15 @@ __device__ __noinline__ uint32_t load_dword_bytes(__amdgpu_buffer_rsrc_t rs, int
   return v;
 }
 
-// Stages the tile's pixels (P rows x up to 64 patches) in LDS as bytes, through aligned
-// dword loads of a range-checked buffer (reads never leave the image).  Row r of the tile
-// starts at byte shift[r] of its LDS row.
+// Stages the tile's pixels (P rows x up to TP patches) in LDS as bytes, through 16-byte loads at
+// dword addresses of a range-checked buffer (reads never leave the image): one per thread and
+// row (a row of 64 patches of 16 has 193), all rows in flight before the LDS writes.  Row r of the
+// tile starts at byte shift[r] of its LDS row.
+typedef unsigned int apc_u32x4 __attribute__((ext_vector_type(4)));
+template <int NT>
 __device__ __forceinline__ int stage_tile(const DensityParams& p, int tile, uint32_t* px, int* shift,
                                           int* py_out, int* px0_out) {
+  constexpr int G = NT / 256, kRows = (kMaxPatch + G - 1) / G;   // threads 256 g + q take rows g, g + G, ...
   const int py = tile / p.tiles_x;
   const int px0 = (tile % p.tiles_x) * kPatchesPerTile;
   const int np = min(kPatchesPerTile, p.gw - px0);
@@ -75,45 +78,34 @@ __device__ __forceinline__ int stage_tile(const DensityParams& p, int tile, uint
   const int total = p.H * p.W * 3;
   const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint8_t*>(p.img), (short)0, total, 0x00020000);
-  const int nd = (row_bytes + 3) / 4 + 1;   // <= 4 * kApcThreads dwords per row
-  // eight rows at a time (P <= 16: one or two batches), all of a thread's loads of a batch in
-  // flight before its LDS writes
+  const int nq = ((row_bytes + 3) / 4 + 1 + 3) / 4;   // 16-byte words per row, at most 256
+  const int q = static_cast<int>(threadIdx.x) & 255, g = static_cast<int>(threadIdx.x) >> 8;
+  const int b00 = py * p.P * p.W * 3 + px0 * p.P * 3;
+  apc_u32x4 v[kRows];
 #pragma unroll
-  for (int r0 = 0; r0 < kMaxPatch; r0 += 8) {
-    if (r0 >= p.P) break;
-    uint32_t v[8][4];
+  for (int k = 0; k < kRows; ++k) {
+    const int r = g + k * G;
+    const int a = ((b00 + r * p.W * 3) & ~3) + 16 * q;
+    if (r < p.P) v[k] = __builtin_amdgcn_raw_buffer_load_b128(rs, q < nq ? static_cast<unsigned>(a) : kNoStore, 0, 0);
+  }
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int r = r0 + q;
-      const int a0 = ((py * p.P + r) * p.W * 3 + px0 * p.P * 3) & ~3;
+  for (int k = 0; k < kRows; ++k) {
+    // the word across the image's end, dword by dword and the last one byte by byte
+    const int r = g + k * G;
+    const int a = ((b00 + r * p.W * 3) & ~3) + 16 * q;
+    if (r < p.P && q < nq && a < total && a + 16 > total) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int dd = static_cast<int>(threadIdx.x) + u * kApcThreads;
-        v[q][u] = (r < p.P && dd < nd) ? load_dword(rs, a0 + 4 * dd) : 0u;
-      }
+      for (int d = 0; d < 4; ++d) v[k][d] = load_dword_bytes(rs, a + 4 * d, total);
     }
+  }
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int a0 = ((py * p.P + r0 + q) * p.W * 3 + px0 * p.P * 3) & ~3;
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int a = a0 + 4 * (static_cast<int>(threadIdx.x) + u * kApcThreads);
-        if (r0 + q < p.P && straddles(a, total)) v[q][u] = load_dword_bytes(rs, a, total);
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int r = r0 + q;
-      if (r < p.P) {
-        const int b0 = (py * p.P + r) * p.W * 3 + px0 * p.P * 3;
-        if (threadIdx.x == 0) shift[r] = b0 - (b0 & ~3);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int dd = static_cast<int>(threadIdx.x) + u * kApcThreads;
-          if (dd < nd) px[r * p.row_dwords + dd] = v[q][u];
-        }
-      }
-    }
+  for (int k = 0; k < kRows; ++k) {
+    const int r = g + k * G;
+    if (r < p.P && q < nq) *reinterpret_cast<apc_u32x4*>(px + r * p.row_dwords + 4 * q) = v[k];
+  }
+  if (static_cast<int>(threadIdx.x) < p.P) {
+    const int b0 = b00 + static_cast<int>(threadIdx.x) * p.W * 3;
+    shift[threadIdx.x] = b0 - (b0 & ~3);
   }
   *py_out = py;
   *px0_out = px0;
@@ -125,8 +117,8 @@ __device__ __forceinline__ float feat_of(uint8_t b) { return static_cast<float>(
 
 // Feature component e = (patch row r, byte cb within the patch row: pixel column, channel)
 // of a tile's patches; patch j of the tile starts at byte j * 3P of each staged row.
-template <int PASS>
-__global__ __launch_bounds__(kApcThreads) void apc_patch_pass(const DensityParams p) {
+template <int PASS, int NT>
+__global__ __launch_bounds__(NT) void apc_patch_pass(const DensityParams p) {
   extern __shared__ __align__(16) uint32_t lds[];
   uint32_t* px = lds;                                             // [P][row_dwords]
   float* inv = reinterpret_cast<float*>(px + p.P * p.row_dwords);  // [64]
@@ -134,27 +126,29 @@ __global__ __launch_bounds__(kApcThreads) void apc_patch_pass(const DensityParam
   const int pb = 3 * p.P;                // bytes of one patch row
   const int cstride = (pb + 3) & ~3;
   __shared__ int shift[kMaxPatch];
-  __shared__ float red[kApcThreads / 64];
+  __shared__ float red[NT / 64];
   const int tile = blockIdx.x;
   // pass 1: the component sums of sum_i T_i (D <= 3 * 16^2, three per thread), requested
   // before the tile so that their loads fly with the tile's
-  constexpr int kCPer = (3 * kMaxPatch * kMaxPatch + kApcThreads - 1) / kApcThreads;
+  constexpr int kCPer = (3 * kMaxPatch * kMaxPatch + NT - 1) / NT;
   float cs[kCPer];
   if (PASS == 1) {
 #pragma unroll
     for (int k = 0; k < kCPer; ++k) {
-      const int e = static_cast<int>(threadIdx.x) + k * kApcThreads;
+      const int e = static_cast<int>(threadIdx.x) + k * NT;
       cs[k] = e < p.D ? p.csum[e] : 0.f;
     }
   }
-  const int j = threadIdx.x >> 2, t = threadIdx.x & 3;
+  // patch j of the tile has kPer threads: t takes 12 of a row's bytes, rg every kRG-th row
+  constexpr int kPer = NT / kPatchesPerTile, kRG = kPer / 4;
+  const int j = threadIdx.x / kPer, t = threadIdx.x & 3, rg = (threadIdx.x % kPer) >> 2;
   float s_inv = 0.f;   // pass 1: 1/||f|| of the thread's patch, requested before the tile
   if (PASS == 1) {
     const int px0_ = (tile % p.tiles_x) * kPatchesPerTile;
     if (j < min(kPatchesPerTile, p.gw - px0_)) s_inv = p.inv_norm[(tile / p.tiles_x) * p.gw + px0_ + j];
   }
   int py, px0;
-  const int np = stage_tile(p, tile, px, shift, &py, &px0);
+  const int np = stage_tile<NT>(p, tile, px, shift, &py, &px0);
   if (PASS == 1) {
     // c = mean_i T_i and phi = ||c||^2 (equal to Eq. 1's mean pairwise cosine), summed by
     // every workgroup in the same fixed order, so that all get the same c_hat
@@ -162,7 +156,7 @@ __global__ __launch_bounds__(kApcThreads) void apc_patch_pass(const DensityParam
     float ss = 0.f;
 #pragma unroll
     for (int k = 0; k < kCPer; ++k) {
-      const int e = static_cast<int>(threadIdx.x) + k * kApcThreads;
+      const int e = static_cast<int>(threadIdx.x) + k * NT;
       const float c = cs[k] * invN;
       if (e < p.D) chat[(e / pb) * cstride + e % pb] = c;
       ss += c * c;
@@ -174,12 +168,12 @@ __global__ __launch_bounds__(kApcThreads) void apc_patch_pass(const DensityParam
   if (PASS == 1) {
     float ss = red[0];
 #pragma unroll
-    for (int i = 1; i < kApcThreads / 64; ++i) ss += red[i];
+    for (int i = 1; i < NT / 64; ++i) ss += red[i];
     const float nc = sqrtf(ss);
     const float ic = (nc > 1e-5f) ? 1.0f / nc : 0.f;   // c_hat = 0 when ||c|| is numerically zero
 #pragma unroll
     for (int k = 0; k < kCPer; ++k) {
-      const int e = static_cast<int>(threadIdx.x) + k * kApcThreads;
+      const int e = static_cast<int>(threadIdx.x) + k * NT;
       if (e < p.D) chat[(e / pb) * cstride + e % pb] *= ic;
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -219,7 +213,7 @@ __global__ __launch_bounds__(kApcThreads) void apc_patch_pass(const DensityParam
         keep[k] = v >= 4 ? 0xffffffffu : ((1u << (8 * v)) - 1u);
       }
 #pragma unroll 2
-      for (int r = 0; r < p.P; ++r) {
+      for (int r = rg; r < p.P; r += kRG) {
         uint32_t x[3];
         row_bytes(r, x);
 #pragma unroll
@@ -230,32 +224,58 @@ __global__ __launch_bounds__(kApcThreads) void apc_patch_pass(const DensityParam
         }
       }
     }
-    sq += __shfl_xor(sq, 1, 64);
-    sq += __shfl_xor(sq, 2, 64);
-    sm += __shfl_xor(sm, 1, 64);
-    sm += __shfl_xor(sm, 2, 64);
-    if (j < np && t == 0) {
+#pragma unroll
+    for (int o = 1; o < kPer; o <<= 1) {
+      sq += __shfl_xor(sq, o, 64);
+      sm += __shfl_xor(sm, o, 64);
+    }
+    if (j < np && t == 0 && rg == 0) {
       const int num = 4 * static_cast<int>(sq) - 1020 * static_cast<int>(sm) + 65025 * p.D;
       const float in = 255.0f / sqrtf(static_cast<float>(num));
       inv[j] = in;
       p.inv_norm[py * p.gw + px0 + j] = in;
     }
     __syncthreads();
-    // tile partial of sum_i T_i, patches added in index order
-    for (int e = threadIdx.x; e < p.D; e += kApcThreads) {
-      const int r = e / pb, cb = e - r * pb;
-      const uint8_t* col = pxb + r * rb + shift[r] + cb;
-      float sum = 0.f;
-#pragma unroll 8
-      for (int jj = 0; jj < np; ++jj) sum += feat_of(col[jj * pb]) * inv[jj];
-      p.partial[static_cast<long long>(tile) * p.D + e] = sum;
+    // tile partial of sum_i T_i: a thread sums eight neighbouring components over every
+    // `parts`-th patch in index order (its bytes of a patch from three dwords, realigned), and the
+    // parts are added in order.  (With one component per thread, every byte took an LDS read of
+    // its own and one of inv.)
+    const int nc8 = (pb + 7) >> 3, cols = p.P * nc8, parts = min(NT / cols, kPatchesPerTile);
+    const int part = static_cast<int>(threadIdx.x) / cols, col = static_cast<int>(threadIdx.x) - part * cols;
+    const int r = col / nc8, cb = (col - r * nc8) * 8;
+    float sum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if (part < parts) {
+      const int o0 = r * rb + shift[r] + cb;
+#pragma unroll 4
+      for (int jj = part; jj < np; jj += parts) {
+        const int o = o0 + jj * pb;
+        const uint32_t* wp = px + (o >> 2);
+        const uint32_t w0 = wp[0], w1 = wp[1], w2 = wp[2];
+        const uint32_t x[2] = {__builtin_amdgcn_alignbyte(w1, w0, o & 3), __builtin_amdgcn_alignbyte(w2, w1, o & 3)};
+        const float s = inv[jj];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) sum[i] += feat_of(static_cast<uint8_t>(x[i >> 2] >> (8 * (i & 3)))) * s;
+      }
+    }
+    __syncthreads();   // the staged bytes make room for the parts
+    float* ps = reinterpret_cast<float*>(lds);
+    if (part < parts) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (cb + i < pb) ps[part * p.D + r * pb + cb + i] = sum[i];
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < p.D; e += NT) {
+      float tot = ps[e];
+      for (int q = 1; q < parts; ++q) tot += ps[q * p.D + e];
+      p.partial[static_cast<long long>(tile) * p.D + e] = tot;
     }
   } else {
     // d_i^2 = sum_e (f_e s - c_hat_e)^2 over the thread's bytes of every row, in row order
     float acc = 0.f;
     if (j < np && nb > 0) {
 #pragma unroll 2
-      for (int r = 0; r < p.P; ++r) {
+      for (int r = rg; r < p.P; r += kRG) {
         uint32_t x[3];
         row_bytes(r, x);
         // 12 values from the thread's first column (the ones past nb, read from the next row or
@@ -270,9 +290,9 @@ __global__ __launch_bounds__(kApcThreads) void apc_patch_pass(const DensityParam
         }
       }
     }
-    acc += __shfl_xor(acc, 1, 64);
-    acc += __shfl_xor(acc, 2, 64);
-    if (j < np && t == 0) p.d[py * p.gw + px0 + j] = sqrtf(acc);
+#pragma unroll
+    for (int o = 1; o < kPer; o <<= 1) acc += __shfl_xor(acc, o, 64);
+    if (j < np && t == 0 && rg == 0) p.d[py * p.gw + px0 + j] = sqrtf(acc);
   }
 }
 
@@ -532,34 +552,59 @@ __global__ __launch_bounds__(64) void apc_pixel_features(const PixelParams p) {
   if (lane < 8) out[lane] = mine;
 }
 
-// Sum of the tile partials per component: 64 components per block, 16 interleaved
-// slices of the tiles per component, combined in a fixed order.
+// Sum of the tile partials per component: SL interleaved slices of the tiles and 1024 / SL
+// components per block, combined in a fixed order.  Latency-bound: 64 slices with 16 loads in
+// flight take up to 1,024 tiles in one round trip (the 770 tiles of a 4K frame 4.7 -> 3.2 us);
+// for few tiles the longer combination costs more (32 tiles: 2.4 against 1.7 us).
+template <int SL>
 __global__ __launch_bounds__(1024) void apc_reduce_c(const DensityParams p) {
-  __shared__ float part[16][64];
-  const int c = threadIdx.x & 63;
-  const int e = blockIdx.x * 64 + c;
-  const int g = threadIdx.x >> 6;
+  constexpr int NC = 1024 / SL, G = SL / 8, U = SL / 4 < 8 ? 8 : SL / 4;
+  __shared__ float part[SL][NC];
+  __shared__ float part2[8][NC];
+  const int c = threadIdx.x % NC, g = threadIdx.x / NC;
+  const int e = blockIdx.x * NC + c;
   float s = 0.f;
   if (e < p.D) {
-    // eight tiles' loads in flight, added in tile order
-    for (int t0 = g; t0 < p.n_tiles; t0 += 16 * 8) {
-      float v[8];
+    // U tiles' loads in flight, added in tile order
+    for (int t0 = g; t0 < p.n_tiles; t0 += SL * U) {
+      float v[U];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int t = t0 + 16 * u;
+      for (int u = 0; u < U; ++u) {
+        const int t = t0 + SL * u;
         v[u] = t < p.n_tiles ? p.partial[static_cast<long long>(t) * p.D + e] : 0.f;
       }
 #pragma unroll
-      for (int u = 0; u < 8; ++u) s += v[u];
+      for (int u = 0; u < U; ++u) s += v[u];
     }
   }
   part[g][c] = s;
   __syncthreads();
+  if constexpr (G > 2) {
+    if (g < 8) {
+      float t = 0.f;
+#pragma unroll
+      for (int i = 0; i < G; ++i) t += part[8 * i + g][c];
+      part2[g][c] = t;
+    }
+    __syncthreads();
+  }
   if (g == 0 && e < p.D) {
     float tot = 0.f;
-    for (int i = 0; i < 16; ++i) tot += part[i][c];
+    if constexpr (G > 2) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) tot += part2[i][c];
+    } else {
+#pragma unroll
+      for (int i = 0; i < SL; ++i) tot += part[i][c];
+    }
     p.csum[e] = tot;
   }
+}
+
+pace_status_t launch_reduce_c(const DensityParams& p, hipStream_t stream) {
+  if (p.n_tiles <= 256) hipLaunchKernelGGL((apc_reduce_c<16>), dim3((p.D + 63) / 64), dim3(1024), 0, stream, p);
+  else hipLaunchKernelGGL((apc_reduce_c<64>), dim3((p.D + 15) / 16), dim3(1024), 0, stream, p);
+  return check_launch("apc_reduce_c");
 }
 
 __global__ __launch_bounds__(1024) void apc_finalize_c(const DensityParams p) {
@@ -1141,6 +1186,23 @@ __global__ __launch_bounds__(kRsThreads) void apc_resize(const ResizeParams p) {
   }
 }
 
+// A patch pass over the image's tiles.  With fewer tiles than CUs a workgroup has its CU to itself
+// and takes 1,024 threads: its phases are chains of memory and LDS round trips that more threads
+// shorten (448 x 448, 32 tiles: passes 7.5 + 7.8 us with 256 threads, 6.0 + 5.4 with 1,024); with
+// more, 256 threads (2156 x 3836, 770 tiles: 13.2 + 12.2 us against 16.0 + 14.4).
+template <int PASS>
+pace_status_t launch_patch_pass(const DensityParams& p, hipStream_t stream) {
+  const int nt = p.n_tiles < 256 ? 1024 : 256;
+  // pixels, 1/norms and c_hat (pass 1); or the parts of the tile's sum (pass 0, at most 8 floats a
+  // thread)
+  size_t lds = (static_cast<size_t>(p.P) * p.row_dwords + kPatchesPerTile +
+                static_cast<size_t>(p.P) * ((3 * p.P + 3) & ~3) + 12) * sizeof(float);
+  if (PASS == 0 && lds < nt * 8 * sizeof(float)) lds = nt * 8 * sizeof(float);
+  if (nt == 1024) hipLaunchKernelGGL((apc_patch_pass<PASS, 1024>), dim3(p.n_tiles), dim3(1024), lds, stream, p);
+  else hipLaunchKernelGGL((apc_patch_pass<PASS, 256>), dim3(p.n_tiles), dim3(256), lds, stream, p);
+  return check_launch("apc_patch_pass");
+}
+
 void size_density(Sizer& s, int H, int W, int P) {
   const int gh = H / P, gw = W / P, N = gh * gw, D = 3 * P * P;
   const int tiles = gh * ((gw + kPatchesPerTile - 1) / kPatchesPerTile);
@@ -1160,8 +1222,7 @@ pace_status_t launch_feature_density(const DensityParams& p, int mode, hipStream
   else hipLaunchKernelGGL((apc_feat_pass<0, kFeatF32>), g0, blk, 0, stream, p);
   pace_status_t st = check_launch("apc_feat_pass<0>");
   if (st != PACE_OK) return st;
-  hipLaunchKernelGGL(apc_reduce_c, dim3((p.D + 63) / 64), dim3(1024), 0, stream, p);
-  if ((st = check_launch("apc_reduce_c")) != PACE_OK) return st;
+  if ((st = launch_reduce_c(p, stream)) != PACE_OK) return st;
   hipLaunchKernelGGL(apc_finalize_c, dim3(1), dim3(1024), 0, stream, p);
   if ((st = check_launch("apc_finalize_c")) != PACE_OK) return st;
   if (mode == kFeatBf16Vec) hipLaunchKernelGGL((apc_feat_pass<1, kFeatBf16Vec>), g1, blk, 0, stream, p);
@@ -1222,15 +1283,10 @@ pace_status_t pace_apc_density(const uint8_t* img, int H, int W, int patch, doub
   float* dws = c.take<float>(p.N);
   p.d = d_out ? d_out : dws;
   p.rho_out = rho_out;
-  const size_t lds = (static_cast<size_t>(patch) * p.row_dwords + kPatchesPerTile +
-                      static_cast<size_t>(patch) * ((3 * patch + 3) & ~3) + 12) * sizeof(float);
-  hipLaunchKernelGGL(apc_patch_pass<0>, dim3(p.n_tiles), dim3(kApcThreads), lds, stream, p);
-  pace_status_t st = check_launch("apc_patch_pass<0>");
+  pace_status_t st = launch_patch_pass<0>(p, stream);
   if (st != PACE_OK) return st;
-  hipLaunchKernelGGL(apc_reduce_c, dim3((p.D + 63) / 64), dim3(1024), 0, stream, p);
-  if ((st = check_launch("apc_reduce_c")) != PACE_OK) return st;
-  hipLaunchKernelGGL(apc_patch_pass<1>, dim3(p.n_tiles), dim3(kApcThreads), lds, stream, p);
-  if ((st = check_launch("apc_patch_pass<1>")) != PACE_OK) return st;
+  if ((st = launch_reduce_c(p, stream)) != PACE_OK) return st;
+  if ((st = launch_patch_pass<1>(p, stream)) != PACE_OK) return st;
   launch_tail(p, stream);
   return check_launch("apc_tail");
 }

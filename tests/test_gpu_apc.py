@@ -130,7 +130,9 @@ def test_density_random_shapes(case):
     np.testing.assert_allclose(rho4(host(rho)), [ref["rho_g"], ref["rho_d"], ref["rho"], ref["phi"]], atol=1e-4)
 
 
-@pytest.mark.parametrize("patch,gh,gw", [(1, 40, 37), (2, 23, 31), (5, 17, 29), (3, 64, 70), (11, 9, 67)])
+@pytest.mark.parametrize("patch,gh,gw", [(1, 40, 37), (2, 23, 31), (5, 17, 29), (3, 64, 70), (11, 9, 67),
+                                         # 256 tiles and more: the passes with 256 threads per tile
+                                         (1, 301, 70), (3, 257, 65), (13, 261, 1), (16, 256, 3)])
 def test_density_small_and_odd_patches(patch, gh, gw):
     """Patch sizes whose rows split unevenly over a patch's four threads (3P bytes: 3, 6, 15, 9
     and 33), with a tile row of more than 64 patches (a second tile per patch row); d_i and rho
