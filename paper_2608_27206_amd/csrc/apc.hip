@@ -796,6 +796,7 @@ void launch_tail(const DensityParams& p, hipStream_t stream) {
 // vertical pass straight to the output.  Shrinks beyond 32x per side, whose spans do not fit
 // a staged tile, take apc_resize_direct (one workgroup per output pixel).
 constexpr int kRsThreads = 256;
+constexpr int kRsRegThreads = 512;   // apc_resize_reg
 constexpr int kRsMaxLds = 64 * 1024;
 
 struct ResizeParams {
@@ -805,6 +806,7 @@ struct ResizeParams {
   int ty, tx;             // output rows / columns per workgroup
   float rx, ry;           // W / oW and H / oH (register path: per-axis constants set on the host)
   float invdx, invdy;     // 1 / (2 max(W, oW)) and 1 / (2 max(H, oH))
+  int small_x, small_y;   // the tap distances of the axis fit 24-bit products and 32-bit sums
   int ntx, nty;           // tap slots per output column / row (upper bound of the tap count)
   int rows_cap;           // input rows staged per workgroup
   int cols_cap;           // input columns staged per workgroup
@@ -854,7 +856,6 @@ __device__ __forceinline__ int make_taps(int o, int n, int m, int slots, float* 
 // weights, lo and count as make_taps up to the order of the normalising sum.  All 64 lanes
 // of the wave must call it together (`valid` false for rows of 16 with no coordinate); the
 // distance numerator is formed in 32 bits when 2 n m fits, which makes the same float.
-constexpr int kRegTaps = 16;
 // keys_cubic without branches (both pieces evaluated, then selected): the same values
 __device__ __forceinline__ float keys_cubic_sel(float x) {
   x = fabsf(x);
@@ -865,21 +866,17 @@ __device__ __forceinline__ float keys_cubic_sel(float x) {
 // ratio = n / m and inv_den = 1 / (2 max(n, m)) come from the host.  The first candidate lo may
 // sit one sample off the one make_taps finds (the centre rounds differently), but the 16
 // candidates still cover the support, whose weights come from the same exact numerators.
-__device__ __forceinline__ void make_taps_row16(int o, bool valid, int n, int m, int slots, float ratio,
+template <int SLOTS>
+__device__ __forceinline__ void make_taps_row16(int o, bool valid, int n, int m, bool small, float ratio,
                                                 float inv_den, float* w_out, int* lo_out, int* count_out) {
   const int lane = threadIdx.x & 63, j = lane & 15;
   const float centre = (static_cast<float>(o) + 0.5f) * ratio;
   const float support = 2.f * fmaxf(1.f, ratio);
   const int lo = max(static_cast<int>(floorf(centre - support - 0.5f)) - 1, 0);
-  float wt = 0.f;
-  if (valid && j < slots && lo + j < n) {
-    float num;
-    if (2ll * n * m < (1ll << 31))
-      num = static_cast<float>((2 * (lo + j) + 1) * m - (2 * o + 1) * n);
-    else
-      num = static_cast<float>((2ll * (lo + j) + 1) * m - (2ll * o + 1) * n);
-    wt = keys_cubic_sel(num * inv_den);
-  }
+  float num;
+  if (small) num = static_cast<float>(__mul24(2 * (lo + j) + 1, m) - __mul24(2 * o + 1, n));
+  else num = static_cast<float>((2ll * (lo + j) + 1) * m - (2ll * o + 1) * n);
+  const float wt = (valid && j < SLOTS && lo + j < n) ? keys_cubic_sel(num * inv_den) : 0.f;
   float sum = wt;
   sum += dpp_f32<kDppQuadXor1>(sum);
   sum += dpp_f32<kDppQuadXor2>(sum);
@@ -890,101 +887,115 @@ __device__ __forceinline__ void make_taps_row16(int o, bool valid, int n, int m,
   const int j1 = bits ? 31 - __builtin_clz(bits) : 0;
   const int j0 = bits ? __builtin_ctz(bits) : 0;
   const int cnt = j1 - j0 + 1;
-  const float inv = 1.f / sum;
-  if (j >= j0 && j <= j1) w_out[j - j0] = wt * inv;
-  if (j >= cnt && j < slots) w_out[j] = 0.f;
+  // lane j's weight goes to slot j - j0; the lanes before j0 clear the slots past the count
+  // (those of a full row wrap around), which the unpredicated loops read
+  const int slot = j >= j0 ? j - j0 : j - j0 + 16;
+  if (slot < SLOTS) w_out[slot] = (j >= j0 && j <= j1) ? wt * (1.f / sum) : 0.f;
   if (j == 0) { *lo_out = lo + j0; *count_out = cnt; }
 }
 
-// The resize with taps of at most kRegTaps per axis (shrinks up to 3x per side) and
-// tx dividing the block: the horizontal pass keeps one output column per thread, its
-// weights in registers, and reads each staged row's bytes as aligned dwords; the vertical
-// pass keeps one (column, channel) and half of the tile's rows per thread.  NT bounds the
-// nonzero horizontal taps: the stretched kernel is nonzero on an open interval of width 4s,
-// which holds at most ceil(4s) + 1 sample points (the extra one when rounding leaves a
-// near-zero weight at an end), so the NT-tap loop runs unpredicated, the weights past a
-// column's count being zero (adding 0 * x leaves every sum bit for bit as it was).  Same
+// The resize for shrinks up to 3x per side, on tiles of TY x 32 output pixels: the horizontal pass
+// keeps one output column per thread, its weights in registers, and reads each staged row's
+// bytes as aligned dwords; the vertical pass keeps one (column, channel) and every fifth row per
+// thread.  NT bounds the nonzero taps of both axes: the stretched kernel is nonzero on an open
+// interval of width 4s, which holds at most ceil(4s) + 1 sample points (the extra one when
+// rounding leaves a near-zero weight at an end), so the NT-tap loops run unpredicated, the
+// weights past a count being zero (adding 0 * x leaves every sum bit for bit as it was).  Same
 // arithmetic, in the same order, as apc_resize.
-template <int NT>
-__global__ __launch_bounds__(kRsThreads) void apc_resize_reg(const ResizeParams p) {
+//   Bound: VALU (a conversion and an FMA per tap and byte, and the taps and staging of the tile).
+// On the 4K frame halved per side, 37.2 -> 25.9 us per call against 16-row tiles of 256 threads with
+// run-time tap counts, dword staging with a test per load, and 64-bit tap distances: unrolled
+// taps in the vertical pass, 16-byte staging, 24-bit products and fewer taps and halo rows per
+// output pixel (16 rows with all else equal: 28.0 us; at 1.4x 44.4 against 32.3).
+template <int NT, int TY>
+__global__ __launch_bounds__(kRsRegThreads) void apc_resize_reg(const ResizeParams p) {
+  constexpr int THREADS = kRsRegThreads;
   constexpr int ND = (3 * NT + 3) / 4 + 1;   // dwords covering 3 NT bytes at any byte shift
-  extern __shared__ float sm[];
-  float* wx = sm + p.o_wx;                      // [tx][ntx], ntx a multiple of 4
-  float* wy = sm + p.o_wy;                      // [ty][nty]
-  int* lox = reinterpret_cast<int*>(sm + p.o_lox);
-  int* loy = reinterpret_cast<int*>(sm + p.o_loy);
-  int* cnx = lox + p.tx;
-  int* cny = loy + p.ty;
-  uint32_t* pix = reinterpret_cast<uint32_t*>(sm + p.o_pix);
+  constexpr int kTx = 32;                    // output columns per workgroup
+  constexpr int SLOTS = (NT + 6) / 4 * 4;    // weights per coordinate: 8, 12 or 16
+  extern __shared__ __align__(16) float sm[];
+  float* wx = sm;                                    // [kTx][SLOTS]
+  float* wy = wx + kTx * SLOTS;                      // [TY][SLOTS]
+  int* lox = reinterpret_cast<int*>(wy + TY * SLOTS);
+  int* cnx = lox + kTx;
+  int* loy = cnx + kTx;
+  int* cny = loy + TY;
+  uint32_t* pix = reinterpret_cast<uint32_t*>(cny + TY);
   float* hb = sm + p.o_h;
-  __shared__ int shift[256];
   const int tid = threadIdx.x;
-  const int ox0 = blockIdx.x * p.tx, oy0 = blockIdx.y * p.ty;
-  const int ncols = min(p.tx, p.oW - ox0), nrows = min(p.ty, p.oH - oy0);
+  const int ox0 = blockIdx.x * kTx, oy0 = blockIdx.y * TY;
+  const int ncols = min(kTx, p.oW - ox0), nrows = min(TY, p.oH - oy0);
   // taps: 16 lanes per output coordinate, the tile's columns first, then its rows
-  for (int b = 0; b < (p.tx + p.ty) * 16; b += kRsThreads) {
+#pragma unroll
+  for (int b = 0; b < (kTx + TY) * 16; b += THREADS) {
     const int item = (b + tid) >> 4;
-    if (item < p.tx)
-      make_taps_row16(ox0 + item, item < ncols, p.W, p.oW, p.ntx, p.rx, p.invdx, wx + item * p.ntx, &lox[item],
-                      &cnx[item]);
-    else {
-      const int r = min(item - p.tx, p.ty - 1);
-      make_taps_row16(oy0 + r, item - p.tx < nrows, p.H, p.oH, p.nty, p.ry, p.invdy, wy + r * p.nty, &loy[r],
-                      &cny[r]);
-    }
+    const bool isx = item < kTx;   // the same in a wave: its four items are all columns or all rows
+    const int k = isx ? item : min(item - kTx, TY - 1);
+    if (isx)
+      make_taps_row16<SLOTS>(ox0 + k, k < ncols, p.W, p.oW, p.small_x != 0, p.rx, p.invdx, wx + k * SLOTS, &lox[k], &cnx[k]);
+    else
+      make_taps_row16<SLOTS>(oy0 + k, item - kTx < nrows, p.H, p.oH, p.small_y != 0, p.ry, p.invdy, wy + k * SLOTS, &loy[k],
+                             &cny[k]);
   }
   __syncthreads();
   const int xlo = lox[0], ylo = loy[0];
   const int xin = lox[ncols - 1] + cnx[ncols - 1] - xlo;
   const int yin = loy[nrows - 1] + cny[nrows - 1] - ylo;
-  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint8_t*>(p.src), (short)0, p.H * p.W * 3, 0x00020000);
-  const int nd = (xin * 3 + 3) / 4 + 1;
   const int total = p.H * p.W * 3;
-  for (int r = tid; r < yin; r += kRsThreads) {
-    const int b0 = (ylo + r) * p.W * 3 + xlo * 3;
-    shift[r] = b0 - (b0 & ~3);
-  }
-  // staging: wave w takes rows w, w + 4, ..., lane l dwords l, l + 64, ...; eight loads in
-  // flight per lane before their LDS writes
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint8_t*>(p.src), (short)0, total, 0x00020000);
+  // staging: 32 lanes per row, lane l the row's 16-byte word l (a row has at most 22: 32 columns
+  // at 3x), five rows' words in flight per thread
+  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+  const int b00 = (ylo * p.W + xlo) * 3, pitch = p.W * 3;
   {
-    const int w = tid >> 6, l = tid & 63;
-    for (int r0 = w; r0 < yin; r0 += 8 * (kRsThreads / 64)) {
-      for (int d = l; d - l < nd; d += 64) {
-        uint32_t v[8];
-        int addr[8];
-        bool ok[8];
+    const int nq = ((xin * 3 + 3) / 4 + 1 + 3) / 4;
+    const int l = tid & 31, g = tid >> 5;
+    constexpr int G = THREADS / 32, U = 5;
+    // only the last rows of the image can have a word across its end
+    const bool edge = b00 + (yin - 1) * pitch + 16 * 32 > total;
+    for (int r0 = g; r0 < yin; r0 += U * G) {
+      u32x4 v[U];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const int r = r0 + u * (kRsThreads / 64);
-          ok[u] = r < yin && d < nd;
-          addr[u] = (((ylo + r) * p.W + xlo) * 3 & ~3) + 4 * d;
-          v[u] = ok[u] ? load_dword(rs, addr[u]) : 0u;
+      for (int u = 0; u < U; ++u) {
+        const int r = r0 + u * G, a = ((b00 + r * pitch) & ~3) + 16 * l;
+        v[u] = __builtin_amdgcn_raw_buffer_load_b128(rs, r < yin && l < nq ? static_cast<unsigned>(a) : kNoStore, 0, 0);
+      }
+      if (edge) {   // dword by dword, and the last one byte by byte
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int r = r0 + u * G, a = ((b00 + r * pitch) & ~3) + 16 * l;
+          if (r < yin && l < nq && a < total && a + 16 > total) {
+#pragma unroll
+            for (int d = 0; d < 4; ++d) v[u][d] = load_dword_bytes(rs, a + 4 * d, total);
+          }
         }
+      }
+      if (l < nq) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (ok[u] && straddles(addr[u], total)) v[u] = load_dword_bytes(rs, addr[u], total);
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (ok[u]) pix[(r0 + u * (kRsThreads / 64)) * p.row_dwords + d] = v[u];
+        for (int u = 0; u < U; ++u)
+          if (r0 + u * G < yin) *reinterpret_cast<u32x4*>(pix + (r0 + u * G) * p.row_dwords + 4 * l) = v[u];
       }
     }
   }
+  // the rows of the horizontal pass's output past the staged ones, which the vertical pass reads
+  // with weight zero
+  for (int e = tid; e < NT * kTx * 3; e += THREADS) hb[yin * kTx * 3 + e] = 0.f;
   __syncthreads();
   // horizontal pass: thread -> output column c, staged rows g, g + G, ...
   {
-    const int c = tid % p.tx, g = tid / p.tx, G = kRsThreads / p.tx;
+    const int c = tid % kTx, g = tid / kTx;
+    constexpr int G = THREADS / kTx;
     if (c < ncols) {
-      float wr[kRegTaps];
+      float wr[SLOTS];
 #pragma unroll
-      for (int q = 0; q < kRegTaps / 4; ++q) {
-        const float4 f = (4 * q < p.ntx) ? *reinterpret_cast<const float4*>(wx + c * p.ntx + 4 * q)
-                                         : make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int q = 0; q < SLOTS / 4; ++q) {
+        const float4 f = *reinterpret_cast<const float4*>(wx + c * SLOTS + 4 * q);
         wr[4 * q] = f.x; wr[4 * q + 1] = f.y; wr[4 * q + 2] = f.z; wr[4 * q + 3] = f.w;
       }
       const int xoff = (lox[c] - xlo) * 3;
       for (int r = g; r < yin; r += G) {
-        const int off = shift[r] + xoff;                       // byte offset in the staged row
+        const int off = ((b00 + r * pitch) & 3) + xoff;        // byte offset in the staged row
         const uint32_t* dp = pix + r * p.row_dwords + (off >> 2);
         const uint32_t sh = static_cast<uint32_t>(off & 3);
         uint32_t d[ND];
@@ -1001,28 +1012,31 @@ __global__ __launch_bounds__(kRsThreads) void apc_resize_reg(const ResizeParams 
           a1 += wr[j] * static_cast<float>((e[(b + 1) >> 2] >> (8 * ((b + 1) & 3))) & 255u);
           a2 += wr[j] * static_cast<float>((e[(b + 2) >> 2] >> (8 * ((b + 2) & 3))) & 255u);
         }
-        float* h = hb + (r * p.tx + c) * 3;
+        float* h = hb + (r * kTx + c) * 3;
         h[0] = a0; h[1] = a1; h[2] = a2;
       }
     }
   }
   __syncthreads();
-  // vertical pass: thread -> (column, channel), half of the tile's output rows
-  if (tid < 6 * ncols) {
-    const int half = tid >= 3 * ncols ? 1 : 0;
-    const int cc = tid - half * 3 * ncols;
-    const int c = cc / 3, ch = cc - 3 * c;
-    const int rmid = (nrows + 1) / 2;
-    for (int r = half * rmid; r < (half ? nrows : rmid); ++r) {
-      const float* w = wy + r * p.nty;
-      const int base = loy[r] - ylo;
-      const int nt = cny[r];
+  // vertical pass: thread -> (column, channel) and every kG-th output row, the taps unrolled to
+  // the bound NT
+  constexpr int kG = THREADS / (3 * kTx);
+  const int vg = tid / (3 * kTx), cc = tid - vg * 3 * kTx;
+  if (vg < kG && cc < 3 * ncols) {
+    uint8_t* dst = p.dst + (static_cast<long long>(oy0) * p.oW + ox0) * 3 + cc;
+    for (int r = vg; r < nrows; r += kG) {
+      const float* h = hb + (loy[r] - ylo) * kTx * 3 + cc;
+      float w[SLOTS];
+#pragma unroll
+      for (int q = 0; q < SLOTS / 4; ++q) {
+        const float4 f = *reinterpret_cast<const float4*>(wy + r * SLOTS + 4 * q);
+        w[4 * q] = f.x; w[4 * q + 1] = f.y; w[4 * q + 2] = f.z; w[4 * q + 3] = f.w;
+      }
       float acc = 0.f;
-#pragma unroll 4
-      for (int j = 0; j < nt; ++j) acc += w[j] * hb[((base + j) * p.tx + c) * 3 + ch];
+#pragma unroll
+      for (int j = 0; j < NT; ++j) acc += w[j] * h[j * kTx * 3];
       const float v = floorf(acc + 0.5f);
-      const int u = static_cast<int>(fminf(fmaxf(v, 0.f), 255.f));
-      p.dst[(static_cast<long long>(oy0 + r) * p.oW + ox0 + c) * 3 + ch] = static_cast<uint8_t>(u);
+      dst[static_cast<long long>(r) * p.oW * 3] = static_cast<uint8_t>(static_cast<int>(fminf(fmaxf(v, 0.f), 255.f)));
     }
   }
 }
@@ -1425,6 +1439,9 @@ pace_status_t pace_apc_downsample(const uint8_t* src, int H, int W, uint8_t* dst
   p.ry = static_cast<float>(H) / static_cast<float>(oH);
   p.invdx = 1.f / static_cast<float>(2ll * (W > oW ? W : oW));
   p.invdy = 1.f / static_cast<float>(2ll * (H > oH ? H : oH));
+  // numerators (2 i + 1) m - (2 o + 1) n with i < n, o < m: factors below 2^23, products below 2^31
+  p.small_x = W < (1 << 22) - 64 && 2ll * W * oW + W < (1ll << 31);
+  p.small_y = H < (1 << 22) - 64 && 2ll * H * oH + H < (1ll << 31);
   if (sx > 32.0 || sy > 32.0) {
     // a staged tile's input span grows with the shrink factor: per output pixel from memory
     hipLaunchKernelGGL(apc_resize_direct, dim3(static_cast<unsigned>(oW) * oH), dim3(kRsThreads), 0, stream, p);
@@ -1434,24 +1451,41 @@ pace_status_t pace_apc_downsample(const uint8_t* src, int H, int W, uint8_t* dst
   // guard tap on each side)
   p.ntx = static_cast<int>(ceil(4.0 * (sx > 1 ? sx : 1))) + 4;
   p.nty = static_cast<int>(ceil(4.0 * (sy > 1 ? sy : 1))) + 4;
-  // 16 x 32 output pixels per workgroup: small enough LDS for three or more workgroups per CU
-  // (the image latency of one is hidden by the others), large enough to amortise the taps' halo
-  int ty = 16, tx = 32;
-  auto plan = [&](int t_y, int t_x, ResizeParams& q) {
+  auto plan = [&](int t_y, int t_x, int extra_rows, ResizeParams& q) {
     q.ty = t_y; q.tx = t_x;
     q.rows_cap = static_cast<int>(ceil((t_y - 1) * sy)) + q.nty + 1;
     q.cols_cap = static_cast<int>(ceil((t_x - 1) * sx)) + q.ntx + 1;
-    q.row_dwords = (q.cols_cap * 3 + 3) / 4 + 2;
+    q.row_dwords = (((q.cols_cap * 3 + 3) / 4 + 2) + 3) & ~3;
     int off = 0;
     q.o_wx = off; off += t_x * q.ntx;
     q.o_wy = off; off += t_y * q.nty;
     q.o_lox = off; off += 2 * t_x;
     q.o_loy = off; off += 2 * t_y;
+    off = (off + 3) & ~3;
     q.o_pix = off; off += q.rows_cap * q.row_dwords;
-    q.o_h = off; off += q.rows_cap * t_x * 3;
+    q.o_h = off; off += (q.rows_cap + extra_rows) * t_x * 3;
     return static_cast<size_t>(off) * 4;
   };
-  size_t lds = plan(ty, tx, p);
+  // Shrinks of up to 3x per side: at most 13 nonzero taps per axis (see apc_resize_reg).
+  const double smax = sx > sy ? sx : sy;
+  const int nz = static_cast<int>(ceil(4.0 * (smax > 1 ? smax : 1))) + 1;
+  if (nz <= 13) {
+    const int NT = nz <= 5 ? 5 : nz <= 9 ? 9 : 13, slots = (NT + 6) / 4 * 4;
+    ResizeParams q = p;
+    q.ntx = q.nty = slots;
+    // tiles of 32 rows while their LDS fits 64 KB (always up to 2x, 54 KB), else of 16
+    int ty = 32;
+    size_t lds_q = plan(ty, 32, NT, q);
+    if (lds_q > kRsMaxLds) lds_q = plan(ty = 16, 32, NT, q);
+    const dim3 g((oW + 31) / 32, (oH + ty - 1) / ty), blk(kRsRegThreads);
+    if (NT == 5) hipLaunchKernelGGL((apc_resize_reg<5, 32>), g, blk, lds_q, stream, q);
+    else if (NT == 9) hipLaunchKernelGGL((apc_resize_reg<9, 32>), g, blk, lds_q, stream, q);
+    else if (ty == 32) hipLaunchKernelGGL((apc_resize_reg<13, 32>), g, blk, lds_q, stream, q);
+    else hipLaunchKernelGGL((apc_resize_reg<13, 16>), g, blk, lds_q, stream, q);
+    return check_launch("apc_resize_reg");
+  }
+  int ty = 16, tx = 32;
+  size_t lds = plan(ty, tx, 0, p);
   while (lds > kRsMaxLds || p.rows_cap > 256) {
     if (ty > 1) ty >>= 1;
     else if (tx > 1) tx >>= 1;
@@ -1459,25 +1493,9 @@ pace_status_t pace_apc_downsample(const uint8_t* src, int H, int W, uint8_t* dst
       hipLaunchKernelGGL(apc_resize_direct, dim3(static_cast<unsigned>(oW) * oH), dim3(kRsThreads), 0, stream, p);
       return check_launch("apc_resize_direct");
     }
-    lds = plan(ty, tx, p);
+    lds = plan(ty, tx, 0, p);
   }
   dim3 grid((oW + tx - 1) / tx, (oH + ty - 1) / ty);
-  const int ntx4 = (p.ntx + 3) / 4 * 4;
-  // nonzero horizontal taps per output column: at most ceil(4 sx) + 1 (see apc_resize_reg)
-  const int nz = static_cast<int>(ceil(4.0 * (sx > 1 ? sx : 1))) + 1;
-  if (ntx4 <= kRegTaps && p.nty <= kRegTaps && kRsThreads % tx == 0 &&
-      6 * tx <= kRsThreads && (tx == 32 || tx == 16)) {
-    ResizeParams q = p;
-    q.ntx = ntx4;
-    const size_t lds_q = plan(ty, tx, q);
-    if (lds_q <= kRsMaxLds) {
-      // ntx4 <= 16 caps ceil(4 sx) at 12, so nz <= 13
-      if (nz <= 5) hipLaunchKernelGGL(apc_resize_reg<5>, grid, dim3(kRsThreads), lds_q, stream, q);
-      else if (nz <= 9) hipLaunchKernelGGL(apc_resize_reg<9>, grid, dim3(kRsThreads), lds_q, stream, q);
-      else hipLaunchKernelGGL(apc_resize_reg<13>, grid, dim3(kRsThreads), lds_q, stream, q);
-      return check_launch("apc_resize_reg");
-    }
-  }
   hipLaunchKernelGGL(apc_resize, grid, dim3(kRsThreads), lds, stream, p);
   return check_launch("apc_resize");
 }

@@ -170,7 +170,9 @@ def _check_resize(img, oh, ow):
                                        ((150, 333), (149, 100)), ((96, 128), (96, 128)),
                                        ((300, 200), (37, 23)), ((64, 64), (2, 2)),
                                        ((2156, 3836), (1078, 1918)), ((250, 200), (100, 80)),
-                                       ((300, 128), (150, 128)), ((210, 330), (90, 150))])
+                                       ((300, 128), (150, 128)), ((210, 330), (90, 150)),
+                                       ((333, 1001), (111, 334)), ((97, 301), (97, 101)), ((301, 99), (101, 99)),
+                                       ((83, 97), (33, 65))])
 def test_resize_parity(shape, out):
     img = wl.make_image(3, *shape)
     _check_resize(img, *out)
