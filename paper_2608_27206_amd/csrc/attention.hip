@@ -16,7 +16,8 @@
 //             LDS reads of the row-major V tile.  For head dim 80 the PV product is
 //             padded to 96 rows.  Writes O (bf16, through LDS so that each row is stored
 //             contiguously) and the natural-log LSE (fp32).  Causal segments (the
-//             prefill), short segments and head dim 128.
+//             prefill), short segments and head dim 128.  Small grids: two such groups of
+//             waves share the keys.
 //
 //  attn_fwd_rot  the same computation for long segments at head dim 80, with 12 waves
 //             per workgroup in three groups that rotate through three phases (see the
@@ -33,8 +34,8 @@
 //             head); K stays in registers, query tiles of 64 rows stream through LDS
 //             (three buffers, up to three workgroups per CU).  P = exp2(S * scale * log2 e -
 //             LSE * log2 e) is the exact normalised probability; each lane accumulates
-//             column sums for its 16 keys in fp32, and one butterfly over the half-wave
-//             finishes the sum.  Writes mass[h, key] once (no atomics, deterministic).  At
+//             column sums for its 16 keys in fp32, and a halving exchange over
+//             the half-wave finishes the sums.  Writes mass[h, key] once (no atomics, deterministic).  At
 //             head dim 80 without a mask it is pipelined inside each wave, one 32 x 32
 //             block at a time.
 //
@@ -285,11 +286,14 @@ constexpr float kRescaleSlack = 8.0f;
 // transposing LDS reads whose source addresses also apply the key permutation that
 // matches the accumulator layout of P^T: A slot (g, 4*rd + j) holds key 8*rd + 4*g + j of
 // each 16-key chunk.
-template <int D, bool CAUSAL>
-__global__ __launch_bounds__(kThreads, 2) void attn_fwd(const FwdParams p) {
+// With GROUPS = 2 (small grids: see fwd_groups) two groups of four waves work on the same 128
+// rows, taking every second key tile each with K and V buffers of their own; their partial O^T,
+// row maxima and row sums are combined at the end.
+template <int D, bool CAUSAL, int GROUPS>
+__global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_fwd(const FwdParams p) {
   using C = FwdCfg<D>;
-  __shared__ __align__(16) uint16_t Ks[2][kBN * C::KS];
-  __shared__ __align__(16) uint16_t Vs[2][kBN * C::VS];
+  __shared__ __align__(16) uint16_t Ksm[GROUPS][2][kBN * C::KS];
+  __shared__ __align__(16) uint16_t Vsm[GROUPS][2][kBN * C::VS];
 
   int h, seg, qt;
   if (CAUSAL) {
@@ -325,7 +329,10 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd(const FwdParams p) {
   if (q0 >= L) return;
   const int kvh = h / p.group;
   // the wave index is wave-uniform: keep it in an SGPR (DMA destinations must be uniform)
-  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane((tid >> 6) & 3);
+  const int grp = GROUPS > 1 ? __builtin_amdgcn_readfirstlane(tid >> 8) : 0;
+  auto& Ks = Ksm[grp];
+  auto& Vs = Vsm[grp];
   const int lane = tid & 63, g = lane >> 5, c32 = lane & 31;
   const int qrow = q0 + w * 32 + c32;
   const int qstride = p.Hq * D;
@@ -378,9 +385,9 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd(const FwdParams p) {
   };
 
   // transposed-read source addresses (elements, within a V tile) for this lane
-  const int grp = lane >> 4, li = lane & 15;
-  const int tr_row = 4 * (grp >> 1) + (li >> 2);          // + 8*rd + 16*chunk
-  const int tr_col = 16 * (grp & 1) + 4 * (li & 3);       // + 32*t (dv)
+  const int lg = lane >> 4, li = lane & 15;
+  const int tr_row = 4 * (lg >> 1) + (li >> 2);          // + 8*rd + 16*chunk
+  const int tr_col = 16 * (lg & 1) + 4 * (li & 3);       // + 32*t (dv)
   const int tr_base = tr_row * C::VS + tr_col;
 
   auto qk = [&](int buf, f32x16* s) __attribute__((always_inline)) {
@@ -475,15 +482,20 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd(const FwdParams p) {
   };
 
   const int kend = CAUSAL ? min(L, q0 + kBM) : L;
-  const int ntiles = (kend + kBN - 1) / kBN;
+  // this group's tiles are tile_of(0) .. tile_of(ntiles - 1)
+  const int all_tiles = (kend + kBN - 1) / kBN;
+  const int ntiles = (all_tiles - grp + GROUPS - 1) / GROUPS;
+  auto tile_of = [&](int i) __attribute__((always_inline)) { return GROUPS * i + grp; };
   // prologue: K(0) and V(0) into buffer 0, K(1) into buffer 1
-  load_k(0, 0);
-  load_v(0, 0);
-  if (ntiles > 1) load_k(1, 1);
+  if (GROUPS == 1 || ntiles > 0) {
+    load_k(tile_of(0), 0);
+    load_v(tile_of(0), 0);
+  }
+  if (ntiles > 1) load_k(tile_of(1), 1);
   wait_vmem();
   __syncthreads();
   f32x16 sa[2], sb[2];
-  qk(0, sa);
+  if (GROUPS == 1 || ntiles > 0) qk(0, sa);
 
   // Iteration t: K(t+1) and V(t) are in LDS.  DMA K(t+2) and V(t+1) into the buffers that
   // held K(t) and V(t-1) (every wave is past their last use: it passed this barrier), then
@@ -496,9 +508,9 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd(const FwdParams p) {
     // every wave is past its reads of K(t) (also the prologue's) before K(t+2) replaces it
     wait_vmem();
     __syncthreads();
-    if (t + 2 < ntiles) load_k(t + 2, buf);
-    if (has_next) load_v(t + 1, buf ^ 1);
-    tile_max(s_cur, t * kBN);
+    if (t + 2 < ntiles) load_k(tile_of(t + 2), buf);
+    if (has_next) load_v(tile_of(t + 1), buf ^ 1);
+    tile_max(s_cur, tile_of(t) * kBN);
     if constexpr (has_next) {
       qk(buf ^ 1, s_next);
       exp_pv(s_cur, buf);
@@ -528,21 +540,58 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd(const FwdParams p) {
   if (t + 1 < ntiles) {
     iteration(std::integral_constant<int, 0>{}, std::true_type{}, t, sa, sb);
     iteration(std::integral_constant<int, 1>{}, std::false_type{}, t + 1, sb, sa);
-  } else {
+  } else if (GROUPS == 1 || ntiles > 0) {
     iteration(std::integral_constant<int, 0>{}, std::false_type{}, t, sa, sb);
+  }
+  if constexpr (GROUPS > 1) {
+    // one barrier per iteration: as many as the first group, which has at most one tile more
+    if (ntiles < (all_tiles + GROUPS - 1) / GROUPS) __syncthreads();
   }
 
   // epilogue: normalise, store O (bf16) and LSE
   const float lp = (l_part[0] + l_part[1]) + (l_part[2] + l_part[3]);
-  const float l = lp + __shfl_xor(lp, 32, 64);
+  float l = lp + __shfl_xor(lp, 32, 64);
+  constexpr int kPartV = (C::NT - 2) * 16 + 2;
+  if constexpr (GROUPS > 1) {
+    static_assert(GROUPS == 2, "two partial results");
+    // group 1's O^T, maxima and sums through LDS (every wave is past its last tile reads), group 0
+    // adds them relative to the larger maximum; a group without tiles has maximum -inf, sum 0
+    float* pk = reinterpret_cast<float*>(&Ksm[0][0][0]) + w * 32 * 64 + lane;      // blocks 0 and 1 of O^T
+    float* pv = reinterpret_cast<float*>(&Vsm[0][0][0]) + w * kPartV * 64 + lane;  // the rest, maximum, sum
+    static_assert(4 * 32 * 64 * sizeof(float) <= sizeof(Ksm), "partials do not fit");
+    __syncthreads();
+    if (grp == 1) {
+#pragma unroll
+      for (int t2 = 0; t2 < C::NT; ++t2)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) (t2 < 2 ? pk : pv)[((t2 & 1) * 16 + r) * 64] = oacc[t2][r];
+      pv[(kPartV - 2) * 64] = m_used;
+      pv[(kPartV - 1) * 64] = l;
+    }
+    __syncthreads();
+    if (grp == 1) return;   // group 0's four waves write the rows
+    const float m1 = pv[(kPartV - 2) * 64], l1 = pv[(kPartV - 1) * 64];
+    const float m = fmaxf(m_used, m1);
+    const float f0 = fast_exp2(m_used - m), f1 = fast_exp2(m1 - m);
+#pragma unroll
+    for (int t2 = 0; t2 < C::NT; ++t2)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) oacc[t2][r] = oacc[t2][r] * f0 + (t2 < 2 ? pk : pv)[((t2 & 1) * 16 + r) * 64] * f1;
+    l = l * f0 + l1 * f1;
+    m_used = m;
+  }
   const float inv_l = 1.f / l;
   if (qrow < L && g == 0 && p.lse)
     p.lse[static_cast<long long>(h) * p.Ntot + s0 + qrow] = (m_used + __builtin_amdgcn_logf(l)) * kLn2;
   // O through each wave's own rows of the K buffers (4 waves x 32 rows fill them exactly),
   // once every wave is past its last tile reads
   static_assert(4 * 32 * (D + 8) <= 2 * kBN * C::KS, "staged O does not fit the K buffers");
-  __syncthreads();
-  store_o_staged<D>(oacc, inv_l, 0, &Ks[0][0] + w * 32 * (D + 8),
+  // with two groups behind the partials in the V buffers; each wave stores only rows that it
+  // staged itself then, so no barrier is needed
+  constexpr int kStage = 4 * kPartV * 64 * 2;   // elements
+  static_assert(GROUPS == 1 || kStage + 4 * 32 * (D + 8) <= GROUPS * 2 * kBN * C::VS, "staged O does not fit");
+  if (GROUPS == 1) __syncthreads();
+  store_o_staged<D, C::NT, GROUPS == 1>(oacc, inv_l, 0, (GROUPS == 1 ? &Ks[0][0] : &Vsm[0][0][0] + kStage) + w * 32 * (D + 8),
                     make_rsrc(p.o + static_cast<long long>(s0) * qstride + h * D, seg_bytes_q), q0 + w * 32, qstride);
 }
 
@@ -1570,39 +1619,36 @@ __global__ __launch_bounds__(kThreads, QSPLIT ? 2 : (D == 80 && !CAUSAL) ? 3 : 2
       buf = (buf == 2) ? 0 : buf + 1;
     }
   }
-  // column sums over the 32 query lanes of each half-wave
+  // Column sums over the 32 query lanes of each half-wave, exchanging halves of what is left to
+  // sum at each step (31 exchanges instead of 5 for each of the 32 sums): rows of 16 lanes by
+  // permlane16_swap, then within a row by DPP.  Lane c32 ends with key set c32 / 16, register
+  // c32 % 16, so every lane stores one key.
+  float x[16];
 #pragma unroll
-  for (int ks = 0; ks < 2; ++ks)
+  for (int r = 0; r < 16; ++r) {
+    const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(macc[0][r]), __float_as_uint(macc[1][r]), false, false);
+    x[r] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+  }
+  const bool b3 = (lane & 8) != 0, b2 = (lane & 4) != 0, b1 = (lane & 2) != 0, b0 = (lane & 1) != 0;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      float x = macc[ks][r];
+  for (int r = 0; r < 8; ++r) x[r] = (b3 ? x[r + 8] : x[r]) + dpp_f32<kDppRowMirror>(b3 ? x[r] : x[r + 8]);
 #pragma unroll
-      for (int o = 16; o >= 1; o >>= 1) x += __shfl_xor(x, o, 64);
-      macc[ks][r] = x;
-    }
+  for (int r = 0; r < 4; ++r) x[r] = (b2 ? x[r + 4] : x[r]) + dpp_f32<kDppRowHalfMirror>(b2 ? x[r] : x[r + 4]);
+#pragma unroll
+  for (int r = 0; r < 2; ++r) x[r] = (b1 ? x[r + 2] : x[r]) + dpp_f32<kDppQuadXor2>(b1 ? x[r] : x[r + 2]);
+  x[0] = (b0 ? x[1] : x[0]) + dpp_f32<kDppQuadXor1>(b0 ? x[0] : x[1]);
+  const int key = (c32 >> 4) * 32 + g * 4 + 8 * ((c32 & 15) >> 2) + (c32 & 3);   // of the wave's 64
   float* mrow = p.mass + static_cast<long long>(h) * p.mass_stride + moff;
   if constexpr (QSPLIT) {
     // the four waves' sums of the same 64 keys, added in wave order
     __shared__ float part[4][64];
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        if (c32 == r) part[w][ks * 32 + g * 4 + 8 * (r >> 2) + (r & 3)] = macc[ks][r];
+    part[w][key] = x[0];
     __syncthreads();
     if (w == 0 && kw0 + lane < kend)
       mrow[kw0 + lane - kst] = ((part[0][lane] + part[1][lane]) + part[2][lane]) + part[3][lane];
-    return;
+  } else {
+    if (kw0 + key < kend) mrow[kw0 + key - kst] = x[0];
   }
-#pragma unroll
-  for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      if (c32 == r) {
-        const int key = kw0 + ks * 32 + g * 4 + 8 * (r >> 2) + (r & 3);
-        if (key < kend) mrow[key - kst] = macc[ks][r];
-      }
-    }
 }
 
 // Segments at least this long (without a causal mask, head dim 80) take the rotation
@@ -1623,6 +1669,18 @@ inline long long blocks_bound(int N, int nseg, int max_seglen, int rows) {
 // 9,328 (each K and V^T tile serves a third of the rows).
 inline bool rot_split(int N, int nseg, int max_seglen, int H) {
   return blocks_bound(N, nseg, max_seglen, kRotSplitBM) * H <= 256;
+}
+
+// Key groups per workgroup of attn_fwd: two where the grid leaves CUs with one workgroup of four
+// waves and its rows see enough key tiles to share.  Measured, one group against two: prefill of 28
+// heads, 1,183 tokens (280 workgroups) 27.9 / 24.7 us, 1,564 (364) 35.6 / 32.2, 2,432 (532) 58.9 /
+// 61.3; of 8 heads, 2,432 (152) 43.4 / 38.1, 5,128 (328) 90.4 / 76.6, 10,677 (672) 240 / 255, 228
+// (16) 11.2 / 13.0, 600 (40) 15.1 / 15.1.  Without a mask all workgroups are long, so they
+// have to fit one per CU: 16 heads, 1,000 patches (128) 17.1 / 15.7, segments of 900, 800 and 700
+// (336) 22.9 / 26.3.
+inline int fwd_groups(const FwdParams& fp, bool causal, int max_seglen) {
+  const long long wgs = blocks_bound(fp.Ntot, fp.nseg, max_seglen, kBM) * fp.Hq;
+  return max_seglen >= 768 && wgs <= (causal ? 384 : 256) ? 2 : 1;
 }
 
 template <int D>
@@ -1656,7 +1714,11 @@ pace_status_t launch_attention(FwdParams fp, bool causal, int max_seglen, const 
     fp.nqt = (max_seglen + kBM - 1) / kBM;
     fp.xcd_classes = fp.Hkv % 8 == 0 ? 8 : fp.Hkv % 4 == 0 ? 4 : fp.Hkv % 2 == 0 ? 2 : 1;
     const int xpc = kNumXcd / fp.xcd_classes, per_class = fp.nqt * fp.nseg * (fp.Hq / fp.xcd_classes);
-    hipLaunchKernelGGL((attn_fwd<D, true>), dim3(static_cast<unsigned>((per_class + xpc - 1) / xpc) * kNumXcd), dim3(kThreads), 0, stream, fp);
+    const dim3 grid(static_cast<unsigned>((per_class + xpc - 1) / xpc) * kNumXcd);
+    if (fwd_groups(fp, true, max_seglen) == 2)
+      hipLaunchKernelGGL((attn_fwd<D, true, 2>), grid, dim3(2 * kThreads), 0, stream, fp);
+    else
+      hipLaunchKernelGGL((attn_fwd<D, true, 1>), grid, dim3(kThreads), 0, stream, fp);
   } else if (D == 80 && max_seglen >= kRotMinSeg) {
     VtParams vp{};
     vp.v = fp.v; vp.vt = const_cast<uint16_t*>(fp.vt); vp.amax = const_cast<uint32_t*>(fp.vt_amax);
@@ -1687,7 +1749,11 @@ pace_status_t launch_attention(FwdParams fp, bool causal, int max_seglen, const 
     }
   } else {
     fp.nqt = (max_seglen + kBM - 1) / kBM;
-    hipLaunchKernelGGL((attn_fwd<D, false>), dim3(fp.nqt * fp.nseg * fp.Hq), dim3(kThreads), 0, stream, fp);
+    const dim3 grid(fp.nqt * fp.nseg * fp.Hq);
+    if (fwd_groups(fp, false, max_seglen) == 2)
+      hipLaunchKernelGGL((attn_fwd<D, false, 2>), grid, dim3(2 * kThreads), 0, stream, fp);
+    else
+      hipLaunchKernelGGL((attn_fwd<D, false, 1>), grid, dim3(kThreads), 0, stream, fp);
   }
   pace_status_t st = check_launch("attn_fwd");
   if (st != PACE_OK || mp == nullptr || nmass == 0) return st;

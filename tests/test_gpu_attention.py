@@ -253,6 +253,33 @@ def test_vit_long_segment_splits_d80(H, sizes):
     np.testing.assert_allclose(mass.sum(1), n, rtol=1e-4)
 
 
+@pytest.mark.parametrize("d,hq,hkv,vis,text", [(128, 4, 2, [700, 0, 1], [100, 1, 63]), (80, 4, 1, [768], [1]),
+                                               (128, 28, 4, [1600], [64]), (128, 28, 4, [1700], [64]),
+                                               (128, 6, 3, [64, 900], [0, 3])])
+def test_prefill_key_groups(d, hq, hkv, vis, text):
+    """The causal forward with its keys split over two groups of waves, beside sequences of one
+    key tile (a group without a tile) and of none, an odd and an even number of tiles; 364 workgroups
+    (split) and 392 (not); KV heads in one, two and four XCD classes."""
+    seqs = [a + b for a, b in zip(vis, text)]
+    cu = np.concatenate([[0], np.cumsum(seqs)]).astype(np.int32)
+    n, nv = int(cu[-1]), sum(vis)
+    q, k, v = (wl.random_bf16(171 + i, (n, h, d)) for i, h in enumerate((hq, hkv, hkv)))
+    cv = np.concatenate([[0], np.cumsum(vis)]).astype(np.int32)
+    from paper_2608_27206_amd import pace
+    import torch
+    say(f"prefill groups d={d} heads={hq}/{hkv} sequences={seqs}")
+    o, lse, m = pace.prefill_attention_with_mass(dev_bf16(q), dev_bf16(k), dev_bf16(v), dev_i32(cu), max(seqs),
+                                                 dev_i32(vis), dev_i32(cv), nv, max(vis), dev_i32(vis), dev_i32(text),
+                                                 max(text))
+    torch.cuda.synchronize()
+    Or, Lr, Mr = oatt.prefill_attention(wl.bf16_bits_to_f64(q), wl.bf16_bits_to_f64(k), wl.bf16_bits_to_f64(v), cu,
+                                        vis, vis, text, 1 / math.sqrt(d))
+    assert np.max(np.abs(host_bf16_to_f64(o) - Or)) <= O_TOL
+    assert np.max(np.abs(host(lse) - Lr)) <= LSE_TOL
+    err, rel = mass_ok(host(m), Mr, max(text))
+    assert err <= 0, f"mass rel err {rel}"
+
+
 def test_prefill_tiny_config():
     w = wl.make_workload(0)
     mass, Mr = _check_prefill(w.prefill)
