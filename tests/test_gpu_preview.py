@@ -92,3 +92,33 @@ def test_preview_block_ragged_windows():
     """A grid whose windows are cut at the right and bottom edges (partial windows)."""
     got, ref, rho, d = _block_case(196, 308, seed=12)
     _check_block(got, ref, "196x308")
+
+
+@pytest.mark.parametrize("patch,gh,gw", [(1, 9, 7), (2, 6, 10), (3, 4, 6), (5, 3, 7), (8, 2, 3), (13, 3, 2), (16, 2, 4)])
+def test_patch_rows_of_every_patch_size(patch, gh, gw):
+    """Patch rows whose 16-byte chunks end inside, at and across a row of the patch: with zero
+    output projections the block is its patch embedding, compared with float64 to the GEMM's
+    tolerance."""
+    from paper_2608_27206_amd import pace
+    import torch
+    rs = np.random.default_rng(patch)
+    img = rs.integers(0, 256, size=(gh * patch, gw * patch, 3), dtype=np.uint8)
+    kin, D = 3 * patch * patch, 80
+    w = {"pe": wl.f32_to_bf16_bits(rs.normal(size=(D, kin)).astype(np.float32))}
+    for k in ("wq", "wk", "wv", "wo"):
+        w[k] = np.zeros((D, D), np.uint16)
+    w["wg"], w["wu"], w["wd"] = np.zeros((8, D), np.uint16), np.zeros((8, D), np.uint16), np.zeros((D, 8), np.uint16)
+    for k in ("bq", "bk", "bv", "bo", "bd"):
+        w[k] = np.zeros(D, np.float32)
+    w["bg"] = w["bu"] = np.zeros(8, np.float32)
+    w["g1"] = w["g2"] = np.ones(D, np.float32)
+    order = rs.permutation(gh * gw).astype(np.int32)
+    say(f"preview patch={patch} grid={gh}x{gw}")
+    out = pace.apc_preview(dev_u8(img), patch, dev_i32(order), dev_i32([0, gh * gw]), gh * gw,
+                           pace.preview_weights_to_device(w, torch.device("cuda")))
+    torch.cuda.synchronize()
+    x = img.reshape(gh, patch, gw, patch, 3).transpose(0, 2, 1, 3, 4).reshape(gh * gw, kin)[order] / 127.5 - 1.0
+    x = wl.bf16_bits_to_f64(wl.f32_to_bf16_bits(x.astype(np.float32)))
+    ref = x @ wl.bf16_bits_to_f64(w["pe"]).T
+    err = np.abs(host_bf16_to_f64(out) - ref) - (2.0 ** -8 * np.abs(ref) + 1e-3 * np.sqrt(np.mean(ref ** 2)))
+    assert err.max() <= 0
