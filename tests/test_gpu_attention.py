@@ -73,6 +73,23 @@ def test_vit_short_windows_single_pass(d):
     _check_vit(q, k, v, cu, d)
 
 
+@pytest.mark.parametrize("d", [80, 128])
+def test_vit_short_windows_without_mass(d):
+    """Windows without the mass take the same single pass: O and LSE bit for bit as with it, also
+    with neither LSE nor mass asked for."""
+    from paper_2608_27206_amd import pace
+    import torch
+    sizes = [64, 16, 0, 1, 33, 64, 63]
+    cu = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    q, k, v = (dev_bf16(x) for x in _vit_case(9, cu, 3, d))
+    o, lse, _ = pace.vit_attention(q, k, v, dev_i32(cu), 64)
+    o2, lse2, m2 = pace.vit_attention(q, k, v, dev_i32(cu), 64, want_mass=False)
+    o3, lse3, _ = pace.vit_attention(q, k, v, dev_i32(cu), 64, want_mass=False, want_lse=False)
+    torch.cuda.synchronize()
+    assert m2 is None and lse3 is None
+    assert torch.equal(o, o2) and torch.equal(o, o3) and torch.equal(lse, lse2)
+
+
 def test_vit_short_windows_large_logits():
     sizes = [64, 7, 64, 40]
     cu = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
