@@ -77,28 +77,30 @@ __global__ __launch_bounds__(256) void preview_patchify(const uint8_t* __restric
 
 // ---------------------------------------------------------------- GEMM
 // C[M, N] = A[M, K] B[N, K]^T.  WM x WN waves, each with MI x NI MFMA tiles of 32 x 32.  K goes in
-// stages of 32 through a ring of ST LDS buffers filled by DMA (buffer to LDS, no registers):
-// stage t + ST - 1 is requested while stage t is multiplied, and the barrier of stage t waits
-// for stage t + 1 only, so a load has ST - 2 stages to arrive.  The fragments of the next half
-// stage are read among the MFMAs of the present one, also across the barrier.  Rows past M or N
-// and chunks past K load as zeros (range check, out-of-range offsets), so tails need no branches.
-//   A stage row holds four 16-byte chunks; chunk c of row r sits in slot c ^ ((r >> 2) & 3), so
-// that the 32 rows that a fragment read touches spread over all LDS banks.  The DMA writes lanes
-// in order, so the swizzle is in the global addresses.
+// stages of 64 through a ring of ST LDS buffers filled by DMA (buffer to LDS, no registers), so that
+// every row of a stage is one 128-byte line (in stages of 32 the loads were 64-byte requests, twice
+// as many, and took 65% of the L2s' request slots).  A stage is four steps of K = 16; the
+// fragments of each are read among the MFMAs of the one before, also across stages: a wave that
+// holds a stage's last fragments meets the others, the stage's buffer takes the next request,
+// and the last MFMAs run under the first reads of the following stage.  Rows past M or N and
+// chunks past K load as zeros (range check, out-of-range offsets), so tails need no branches.
+//   A stage row holds eight 16-byte chunks; chunk c of row r sits in slot c ^ ((r >> 1) & 7), so
+// that the rows that a fragment read touches spread over all LDS banks.  The DMA writes lanes in
+// order, so the swizzle is in the global addresses.
 //   The product is formed as C^T (B's rows are the MFMA's A operand): a lane then holds four
 // neighbouring columns of one row, which makes SwiGLU's gate and up neighbours in one lane; the
 // tile leaves through LDS so that rows are stored in 16-byte chunks, and a residual tile comes
 // the same way (read straight into the lanes it cost 20 us of a 64-us round of tiles).
-//   Bound: MFMA.  What is left is the last round of tiles, the burst of stores (and residual
-// loads) when a round ends, and about a third of the issue slots in the loop: one stage of a
-// 256 x 256 tile takes 0.85-0.9 us for 1,024 MFMA cycles per SIMD.  Measured against the 128 x 128
-// register-staged kernel before it, 42,196 rows: N = K = 1,280 with residual 337 -> 214 us; N =
-// 6,848, K = 1,280 with SwiGLU 1,211 -> 742 us (997 TFLOP/s); N = 1,280, K = 3,424 with residual 661
-// -> 454 us; 8,192^3 1,590 -> 941 us (1,169 TFLOP/s).  Tried on the same shapes: 4 x 4 MFMA tiles
-// per wave with four waves (1,080 TFLOP/s at 8,192^3: one wave per SIMD does not hide its own LDS
-// reads), two 128 x 256 workgroups per CU with a ring of three (1,022), no fragments ahead of the
-// barrier (1,144).
-constexpr int kGK = 32;                      // K per stage
+//   Bound: MFMA.  At 8,192^3 the matrix cores are busy 68% of the cycles and the clock falls to
+// 1.6 GHz; at K = 1,280 47%, since a tile's first loads and the burst of stores (and residual
+// loads) at the end of a round take a third of its time.  Measured against the 128 x 128
+// register-staged kernel before it, 42,196 rows: N = K = 1,280 with residual 337 -> 197 us; N =
+// 6,848, K = 1,280 with SwiGLU 1,211 -> 712 us (1,038 TFLOP/s); N = 1,280, K = 3,424 with residual
+// 661 -> 401 us; 8,192^3 1,590 -> 868 us (1,267 TFLOP/s).  Stages of 32 in a ring of four: 205, 744, 446
+// and 920 us.  Tried with stages of 32, TFLOP/s at 8,192^3 against 1,169: 4 x 4 MFMA tiles per wave
+// with four waves 1,080 (one wave per SIMD does not hide its own LDS reads), two 128 x 256
+// workgroups per CU with a ring of three 1,022, no fragments ahead of the barrier 1,144.
+constexpr int kGK = 64;                      // K per stage: a row is one 128-byte line
 
 enum { kEpiBias = 0, kEpiResidual = 1, kEpiSwiglu = 2 };
 
@@ -136,9 +138,11 @@ __device__ __forceinline__ void g_dma16(gi32x4 r, unsigned lds, unsigned voff) {
 }
 template <int N>
 __device__ __forceinline__ void g_wait() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
+// the same, and the wave's LDS reads have returned
+template <int N>
+__device__ __forceinline__ void g_wait_lds() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(N) : "memory"); }
 
-// Workgroup barrier without the wait for LDS reads in flight: the buffers that they read are
-// overwritten only two barriers later.
+// Workgroup barrier alone: the waits before it say what it orders.
 __device__ __forceinline__ void g_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
 template <int MI, int NI, int WM, int WN, int ST>
@@ -146,7 +150,7 @@ __global__ __launch_bounds__(64 * WM * WN, MI * NI > 8 ? 1 : 2) void gemm_bf16_n
   constexpr int BM = 32 * MI * WM, BN = 32 * NI * WN;
   constexpr int NW = WM * WN, kGThreads = 64 * NW;
   constexpr int kStage = (BM + BN) * kGK;            // elements per stage
-  constexpr int kInst = (BM + BN) / 16;              // wave-wide DMAs per stage, 16 rows each
+  constexpr int kInst = (BM + BN) / 8;               // wave-wide DMAs per stage, 8 rows each
   constexpr int kPW = kInst / NW;              // per wave
   static_assert(kInst % NW == 0, "every wave issues the same DMAs");
   constexpr int kLds = ST * kStage > BM * BN ? ST * kStage : BM * BN;
@@ -167,20 +171,18 @@ __global__ __launch_bounds__(64 * WM * WN, MI * NI > 8 ? 1 : 2) void gemm_bf16_n
   const gi32x4 ra = g_rsrc(p.A, static_cast<unsigned>(static_cast<long long>(p.M) * p.K * 2));
   const gi32x4 rb = g_rsrc(p.B[z], static_cast<unsigned>(static_cast<long long>(p.N) * p.K * 2));
 
-  // this lane's chunk of DMA i (wave w issues i = w, w + 8, ...; the first BM / 16 are A's rows)
+  // this lane's chunk of DMA i (wave w issues i = w, w + NW, ...; the first BM / 8 are A's rows)
   unsigned off[kPW];
-  int kc = 0;   // first k of the lane's chunk, the same in each: row >> 2 depends on the lane only
-  {
-    const int slot = lane & 3, r16 = lane >> 2;
-    kc = (slot ^ ((r16 >> 2) & 3)) * 8;
+  // row of the DMA's eight, first k of the chunk (NW is even: i's parity is w's)
+  static_assert(NW % 2 == 0 && (BM / 8) % 2 == 0, "swizzle of odd DMAs");
+  const int r8 = lane >> 3, kc = ((lane & 7) ^ (4 * (w & 1) + (r8 >> 1))) * 8;
 #pragma unroll
-    for (int u = 0; u < kPW; ++u) {
-      const int i = w + NW * u;
-      const bool isa = i < BM / 16;
-      const int row = isa ? bm + i * 16 + r16 : bn + (i - BM / 16) * 16 + r16;
-      // rows past the end lie past the buffer's range
-      off[u] = row < (isa ? p.M : p.N) ? static_cast<unsigned>((static_cast<long long>(row) * p.K + kc) * 2) : kGOut;
-    }
+  for (int u = 0; u < kPW; ++u) {
+    const int i = w + NW * u;
+    const bool isa = i < BM / 8;
+    const int row = isa ? bm + i * 8 + r8 : bn + (i - BM / 8) * 8 + r8;
+    // rows past the end lie past the buffer's range
+    off[u] = row < (isa ? p.M : p.N) ? static_cast<unsigned>((static_cast<long long>(row) * p.K + kc) * 2) : kGOut;
   }
   const unsigned lds0 = static_cast<unsigned>(reinterpret_cast<unsigned long long>((g_lds_char*)(const void*)lds));
   auto load = [&](int t, int buf) __attribute__((always_inline)) {
@@ -190,13 +192,13 @@ __global__ __launch_bounds__(64 * WM * WN, MI * NI > 8 ? 1 : 2) void gemm_bf16_n
     for (int u = 0; u < kPW; ++u) {
       const int i = w + NW * u;
       const unsigned o = in_k ? off[u] + static_cast<unsigned>(t) * (kGK * 2) : kGOut;
-      g_dma16(i < BM / 16 ? ra : rb, base + i * 1024, o);
+      g_dma16(i < BM / 8 ? ra : rb, base + i * 1024, o);
     }
   };
-  // fragment reads: row r of the stage at byte 64 r, chunk c in slot c ^ ((r >> 2) & 3)
-  const int s0 = (g ^ ((c32 >> 2) & 3)) * 8;   // half stage 0; half stage 1 is s0 ^ 16 (elements)
+  // fragment reads: row r of the stage at byte 128 r, chunk c in slot c ^ ((r >> 1) & 7)
+  const int sw = (c32 >> 1) & 7;
   auto frags = [&](int buf, int kk, gbf16x8* a, gbf16x8* b) __attribute__((always_inline)) {
-    const uint16_t* st = lds + buf * kStage + c32 * kGK + (kk ? (s0 ^ 16) : s0);
+    const uint16_t* st = lds + buf * kStage + c32 * kGK + (((2 * kk + g) ^ sw) * 8);
 #pragma unroll
     for (int j = 0; j < NI; ++j) b[j] = *reinterpret_cast<const gbf16x8*>(st + (BM + wn + 32 * j) * kGK);
 #pragma unroll
@@ -224,38 +226,53 @@ __global__ __launch_bounds__(64 * WM * WN, MI * NI > 8 ? 1 : 2) void gemm_bf16_n
   };
 
   const int nk = (p.K + kGK - 1) / kGK;
-  // requested before stage 0: stages 0 .. ST - 2
 #pragma unroll
-  for (int s = 0; s < ST - 1; ++s)
+  for (int s = 0; s < ST; ++s)
     if (s < nk) load(s, s);
-  gbf16x8 a0[MI], b0[NI], a1[MI], b1[NI];
-  int cur = 0;   // buffer of stage t
-  auto next = [](int b) { return b == ST - 1 ? 0 : b + 1; };
-  if (nk >= ST - 1) g_wait<(ST - 2) * kPW>(); else g_wait<0>();
+  if (nk >= ST) g_wait<(ST - 1) * kPW>(); else g_wait<0>();
   g_barrier();
+  gbf16x8 a0[MI], b0[NI], a1[MI], b1[NI];
   frags(0, 0, a0, b0);
-  // stage t: its first half is in a0 / b0.  Past the barrier stage t + 1 is in LDS and every
-  // wave is done with stage t - 1, whose buffer stage t + ST - 1 takes.
-  auto stage = [&](int t, auto LAST) __attribute__((always_inline)) {
-    constexpr bool last = decltype(LAST)::value;
-    if constexpr (!last) {
-      if (t + ST - 2 < nk) g_wait<(ST - 3) * kPW>(); else g_wait<0>();
-      g_barrier();
-      if (t + ST - 1 < nk) load(t + ST - 1, cur == 0 ? ST - 1 : cur - 1);
-    }
-    __builtin_amdgcn_sched_barrier(0);
+  int cur = 0;   // buffer of stage t
+  // Stage t: its first fragments are in a0 / b0.  Once a wave holds the last ones in registers it
+  // meets the others; then stage t + 1 is in LDS, the buffer of stage t takes stage t + ST, and
+  // the last MFMAs run under the first reads of stage t + 1.
+  for (int t = 0; t + 1 < nk; ++t) {
+    const int nxt = cur == ST - 1 ? 0 : cur + 1;
     frags(cur, 1, a1, b1);
     mul(a0, b0);
     spread();
     __builtin_amdgcn_sched_barrier(0);
-    cur = next(cur);
-    if constexpr (!last) frags(cur, 0, a0, b0);
+    frags(cur, 2, a0, b0);
     mul(a1, b1);
-    if constexpr (!last) spread();
+    spread();
     __builtin_amdgcn_sched_barrier(0);
-  };
-  for (int t = 0; t + 1 < nk; ++t) stage(t, std::false_type{});
-  stage(nk - 1, std::true_type{});
+    frags(cur, 3, a1, b1);
+    mul(a0, b0);
+    spread();
+    __builtin_amdgcn_sched_barrier(0);
+    if (t + ST <= nk) g_wait_lds<(ST - 2) * kPW>(); else g_wait_lds<0>();
+    g_barrier();
+    if (t + ST < nk) load(t + ST, cur);
+    frags(nxt, 0, a0, b0);
+    mul(a1, b1);
+    spread();
+    __builtin_amdgcn_sched_barrier(0);
+    cur = nxt;
+  }
+  // the last stage: only the chunks of 16 that K has
+  const int last = (p.K - (nk - 1) * kGK + 15) / 16;
+  if (last > 1) frags(cur, 1, a1, b1);
+  mul(a0, b0);
+  if (last > 1) {
+    if (last > 2) frags(cur, 2, a0, b0);
+    mul(a1, b1);
+  }
+  if (last > 2) {
+    if (last > 3) frags(cur, 3, a1, b1);
+    mul(a0, b0);
+  }
+  if (last > 3) mul(a1, b1);
 
   // epilogue: register 4 jj + ii of tile (i, j) is row wm + 32 i + c32, column
   // wn + 32 j + 8 jj + 4 g + ii.  The bf16 tile goes through LDS, once every wave has read its
@@ -396,8 +413,8 @@ void launch_tile(GemmParams p, int nz, hipStream_t stream) {
 
 // Tiles of 256 x 256 (one workgroup per CU) use the matrix cores best, but come in rounds of 256;
 // tiles of 64 x 128 fill the chip from small products on.  On 42,196 x 1,280 x 1,280 the large
-// tiles ran 4 rounds of 52 us at 640 TFLOP/s against 452 TFLOP/s with the small ones; on
-// 1,024 x 1,280 x 1,280 (20 large tiles) 32.5 us against 12.3.  So one round of large tiles costs
+// tiles ran 4 rounds of 52 us at 640 TFLOP/s against 452 TFLOP/s with the small ones (both with
+// stages of 32); on 1,024 x 1,280 x 1,280 (20 large tiles) 32.5 us against 12.3.  So one round of large tiles costs
 // as much as about 156 of them in small ones, and a launch of small ones at least 0.3 of a round.
 // The rows go to whichever of these is the shortest: large tiles alone, small ones alone, or the
 // full rounds in large and the remaining rows in small tiles.
@@ -417,7 +434,7 @@ pace_status_t launch_gemm(GemmParams p, int nz, hipStream_t stream) {
   if (m0 > 0) {
     GemmParams q = p;
     q.M = m0;
-    launch_tile<4, 2, 2, 4, 4>(q, nz, stream);
+    launch_tile<4, 2, 2, 4, 2>(q, nz, stream);
   }
   if (m0 < p.M) {
     GemmParams q = p;
@@ -425,7 +442,7 @@ pace_status_t launch_gemm(GemmParams p, int nz, hipStream_t stream) {
     q.A += static_cast<long long>(m0) * p.K;
     if (q.R != nullptr) q.R += static_cast<long long>(m0) * p.N;
     for (int z = 0; z < nz; ++z) q.C[z] += static_cast<long long>(m0) * nc;
-    launch_tile<2, 1, 1, 4, 6>(q, nz, stream);
+    launch_tile<2, 1, 1, 4, 3>(q, nz, stream);
   }
   return check_launch("gemm_bf16_nt");
 }
