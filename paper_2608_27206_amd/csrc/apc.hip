@@ -720,7 +720,12 @@ __global__ __launch_bounds__(1024) void apc_finalize_c(const DensityParams p) {
 }
 
 constexpr int kTailR = 48;       // most distances per thread held in registers: up to 49,152 patches
-constexpr int kTailBins = 4096;  // value bins over [0, 2], the range of d
+// Value bins over [0, 2], the range of d (the last bin takes everything above): two 16-bit counts
+// per word (at most 1,024 x 48 distances).  More of them for many distances, so that the
+// threshold's bin holds few candidates: the 42,196 distances of a 4K frame's embeddings, which lie
+// close together, took 20.5 us in 4,096 bins (over 256 candidates: radix passes), 13.5 in
+// 16,384, 13.3 in 32,768; those of its pixels 9.7, 9.6 and 10.0.
+template <int R> constexpr int kTailBins = R > 4 ? 16384 : 4096;
 constexpr int kTailCand = 256;   // candidates ranked by direct comparison
 
 struct TailAdd { __device__ float operator()(float a, float b) const { return a + b; } };
@@ -728,14 +733,16 @@ struct TailAdd { __device__ float operator()(float a, float b) const { return a 
 // Sum of the n_tail largest distances, then rho_d and rho.  d >= 0, so the raw bit patterns
 // order like the values.  With the distances in registers (thread t holds patches
 // j * 1024 + t, j < R; R = 4, 16, 32, 44 or 48, the fewest that hold the patch count, so that
-// smaller images do not walk 48 slots per thread): a histogram of floor(d * 2048) (monotone
+// smaller images do not walk 48 slots per thread): a histogram over kTailBins value bins (monotone
 // in d, clamped), the bin b* that
 // holds the n_tail-th largest value, the threshold T (the need-th largest key in bin b*,
 // by direct comparison among the bin's few candidates, or a radix select when it holds
 // many ties), and sum = (sum of d > T) + need_eq * T, reduced in a fixed order.
 template <int R>
 __global__ __launch_bounds__(1024) void apc_tail(const DensityParams p) {
-  __shared__ __align__(16) uint32_t hist[kTailBins];
+  constexpr int BINS = kTailBins<R>, PB = BINS / 1024, PW = PB / 2;   // bins and words per thread
+  constexpr float kPerUnit = BINS / 2;
+  __shared__ __align__(16) uint32_t hist[BINS / 2];
   __shared__ uint32_t rhist[4 * 256];
   __shared__ uint32_t cand_key[kTailCand];
   __shared__ int cand_idx[kTailCand];
@@ -752,7 +759,8 @@ __global__ __launch_bounds__(1024) void apc_tail(const DensityParams p) {
     // later step as ordinary zeros: as n_tail <= N, the top n_tail values, T and the sum are
     // those of the N distances (a tie at 0 adds 0), and no step needs a per-slot range test.
     const uint32_t pad = static_cast<uint32_t>(1024 * R - p.N);
-    for (int i = tid; i < kTailBins; i += 1024) hist[i] = i == 0 ? pad : 0u;
+#pragma unroll
+    for (int i = 0; i < PW; ++i) hist[i * 1024 + tid] = i + tid == 0 ? pad : 0u;
     rhist[tid] = 0u;
     if (tid < 8) misc[tid] = 0u;
     uint32_t key[R];
@@ -765,36 +773,45 @@ __global__ __launch_bounds__(1024) void apc_tail(const DensityParams p) {
     const bool rem_live = tid < (p.N & 1023);
 #pragma unroll
     for (int j = 0; j < R; ++j) {
-      const int bin = static_cast<int>(fminf(__uint_as_float(key[j]) * 2048.f, static_cast<float>(kTailBins - 1)));
-      if (j < jfull || (j == jfull && rem_live)) atomicAdd(&hist[bin], 1u);
+      const int bin = static_cast<int>(fminf(__uint_as_float(key[j]) * kPerUnit, static_cast<float>(BINS - 1)));
+      if (j < jfull || (j == jfull && rem_live)) atomicAdd(&hist[bin >> 1], 1u << (16 * (bin & 1)));
     }
     __syncthreads();
-    // thread t covers bins 4095 - 4t down to 4092 - 4t (descending)
+    // thread t covers the bins BINS - PB (t + 1) .. BINS - PB t - 1 (descending with t)
     {
-      const int bhi = kTailBins - 1 - 4 * tid;
-      const uint4 h4 = *reinterpret_cast<const uint4*>(&hist[bhi - 3]);
-      const uint32_t cs[4] = {h4.w, h4.z, h4.y, h4.x};
-      const uint32_t tot = cs[0] + cs[1] + cs[2] + cs[3];
+      const int blo = BINS - PB * (tid + 1);
+      uint32_t hw[PW];
+#pragma unroll
+      for (int q = 0; q < PW / 2; ++q) {
+        const uint2 h2 = *reinterpret_cast<const uint2*>(&hist[blo / 2 + 2 * q]);
+        hw[2 * q] = h2.x; hw[2 * q + 1] = h2.y;
+      }
+      uint32_t tot = 0u;
+#pragma unroll
+      for (int q = 0; q < PW; ++q) tot += (hw[q] & 0xffffu) + (hw[q] >> 16);
       const uint32_t incl = wave_incl_scan(tot);
       if (lane == 63) wt[w] = incl;
       __syncthreads();
       uint32_t before = incl - tot;
       for (int i = 0; i < w; ++i) before += wt[i];
       const uint32_t K = static_cast<uint32_t>(p.n_tail);
+      if (before < K && before + tot >= K) {   // one thread
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if (before < K && before + cs[q] >= K) { misc[0] = bhi - q; misc[1] = K - before; }
-        before += cs[q];
+        for (int q = PB - 1; q >= 0; --q) {
+          const uint32_t c = (q & 1) ? hw[q >> 1] >> 16 : hw[q >> 1] & 0xffffu;
+          if (before < K && before + c >= K) { misc[0] = blo + q; misc[1] = K - before; }
+          before += c;
+        }
       }
     }
     __syncthreads();
     const int bstar = static_cast<int>(misc[0]);
     const int need = static_cast<int>(misc[1]);   // 1 <= need <= count of bin b*
-    // d * 2048 is exact, so bin b* holds exactly the keys in [b*/2048, (b*+1)/2048), the
-    // last bin everything from 4095/2048 up
-    const uint32_t lo = __float_as_uint(static_cast<float>(bstar) * (1.f / 2048.f));
-    const uint32_t span = (bstar == kTailBins - 1) ? 0xffffffffu - lo
-                          : __float_as_uint(static_cast<float>(bstar + 1) * (1.f / 2048.f)) - lo;
+    // d * kPerUnit is exact, so bin b* holds exactly the keys in [b*, b* + 1) / kPerUnit, the last
+    // bin everything from there up
+    const uint32_t lo = __float_as_uint(static_cast<float>(bstar) * (1.f / kPerUnit));
+    const uint32_t span = (bstar == BINS - 1) ? 0xffffffffu - lo
+                          : __float_as_uint(static_cast<float>(bstar + 1) * (1.f / kPerUnit)) - lo;
 #pragma unroll
     for (int j = 0; j < R; ++j) {
       if (key[j] - lo < span) {
