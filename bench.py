@@ -305,7 +305,7 @@ def build_workload_step(a, torch, np, pace, wl, dev):
             "prefill": ("mfma", flop_pre),
         })
         flop_attn = 4.0 * dv * Hv * float(np.sum(win_sizes ** 2)) + flop_full + flop_pre
-        roof = ("vit_fwd", "pace_vit_attention call on the full-attention segments: attn_vt_clear + attn_v_amax + "
+        roof = ("vit_fwd", "pace_vit_attention call on the full-attention segments: attn_v_amax + "
                            f"attn_vt_prep + attn_fwd_rot<80> ({Np:,} patches in {nseg} segment(s) x {Hv} heads); "
                            "attn_fwd_rot is 99% of it")
         cfg.update({"images": [f"{im.shape[1]}x{im.shape[0]}" for im in w.images], "vit_patches": int(Np),
