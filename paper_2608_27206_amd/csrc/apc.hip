@@ -58,11 +58,13 @@ struct DensityParams {
 __device__ __forceinline__ uint32_t load_dword(__amdgpu_buffer_rsrc_t rs, int a) {
   return __builtin_amdgcn_raw_buffer_load_b32(rs, static_cast<unsigned>(a), 0, 0);
 }
-__device__ __forceinline__ bool straddles(int a, int total) { return a < total && a + 4 > total; }
-__device__ __noinline__ uint32_t load_dword_bytes(__amdgpu_buffer_rsrc_t rs, int a, int total) {
+// Whether the `n` bytes from a on reach across the end (an image may end just below 2^31 bytes, where
+// a + n does not fit an int).
+__device__ __forceinline__ bool straddles(int a, int n, int total) { return a < total && a > total - n; }
+__device__ __noinline__ uint32_t load_dword_bytes(__amdgpu_buffer_rsrc_t rs, unsigned a, unsigned total) {
   uint32_t v = 0;
-  for (int k = 0; k < 4 && a + k < total; ++k)
-    v |= static_cast<uint32_t>(__builtin_amdgcn_raw_buffer_load_b8(rs, static_cast<unsigned>(a + k), 0, 0)) << (8 * k);
+  for (unsigned k = 0; k < 4 && a + k < total; ++k)
+    v |= static_cast<uint32_t>(__builtin_amdgcn_raw_buffer_load_b8(rs, a + k, 0, 0)) << (8 * k);
   return v;
 }
 
@@ -97,9 +99,9 @@ __device__ __forceinline__ int stage_tile(const DensityParams& p, int tile, uint
     // the word across the image's end, dword by dword and the last one byte by byte
     const int r = g + k * G;
     const int a = ((b00 + r * p.W * 3) & ~3) + 16 * q;
-    if (r < p.P && q < nq && a < total && a + 16 > total) {
+    if (r < p.P && q < nq && straddles(a, 16, total)) {
 #pragma unroll
-      for (int d = 0; d < 4; ++d) v[k][d] = load_dword_bytes(rs, a + 4 * d, total);
+      for (int d = 0; d < 4; ++d) v[k][d] = load_dword_bytes(rs, static_cast<unsigned>(a) + 4 * d, total);
     }
   }
 #pragma unroll
@@ -1063,7 +1065,7 @@ __global__ __launch_bounds__(kRsRegThreads) void apc_resize_reg(const ResizePara
     const int l = tid & 31, g = tid >> 5;
     constexpr int G = THREADS / 32, U = 5;
     // only the last rows of the image can have a word across its end
-    const bool edge = b00 + (yin - 1) * pitch + 16 * 32 > total;
+    const bool edge = b00 + (yin - 1) * pitch > total - 16 * 32;
     for (int r0 = g; r0 < yin; r0 += U * G) {
       u32x4 v[U];
 #pragma unroll
@@ -1075,9 +1077,9 @@ __global__ __launch_bounds__(kRsRegThreads) void apc_resize_reg(const ResizePara
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           const int r = r0 + u * G, a = ((b00 + r * pitch) & ~3) + 16 * l;
-          if (r < yin && l < nq && a < total && a + 16 > total) {
+          if (r < yin && l < nq && straddles(a, 16, total)) {
 #pragma unroll
-            for (int d = 0; d < 4; ++d) v[u][d] = load_dword_bytes(rs, a + 4 * d, total);
+            for (int d = 0; d < 4; ++d) v[u][d] = load_dword_bytes(rs, static_cast<unsigned>(a) + 4 * d, total);
           }
         }
       }
@@ -1269,7 +1271,7 @@ __global__ __launch_bounds__(kRsThreads) void apc_resize(const ResizeParams p) {
     }
 #pragma unroll
     for (int u = 0; u < 8; ++u)
-      if (slot[u] >= 0 && straddles(addr[u], total)) v[u] = load_dword_bytes(rs, addr[u], total);
+      if (slot[u] >= 0 && straddles(addr[u], 4, total)) v[u] = load_dword_bytes(rs, addr[u], total);
 #pragma unroll
     for (int u = 0; u < 8; ++u)
       if (slot[u] >= 0) pix[slot[u]] = v[u];

@@ -150,6 +150,22 @@ def test_density_small_and_odd_patches(patch, gh, gw):
     np.testing.assert_allclose(rho4(host(rho)), [ref["rho_g"], ref["rho_d"], ref["rho"], ref["phi"]], atol=1e-4)
 
 
+def test_density_of_an_image_just_below_2_31_bytes():
+    """The last patch ends in a word across the image's end whose byte offset plus length does not fit
+    an int: a copy of the first patch there has the first patch's distance, bit for bit (norms are
+    exact integer sums, and a patch's terms are added in the same order wherever it lies)."""
+    from paper_2608_27206_amd import pace
+    import torch
+    P, gh, gw = 3, 13, 6118187
+    H, W = gh * P, gw * P
+    assert 2 ** 31 - 16 < 3 * H * W < 2 ** 31 and 3 * H * W % 4
+    say(f"density {H}x{W} patch {P}")
+    img = torch.empty(H, W, 3, dtype=torch.uint8, device="cuda").random_(1, 256)
+    img[-P:, -P:] = img[:P, :P]
+    _, d = pace.apc_density(img, P)
+    assert float(d[-1]) == float(d[0])
+
+
 def _check_resize(img, oh, ow):
     from paper_2608_27206_amd import pace
     import torch
@@ -176,6 +192,23 @@ def _check_resize(img, oh, ow):
 def test_resize_parity(shape, out):
     img = wl.make_image(3, *shape)
     _check_resize(img, *out)
+
+
+def test_resize_of_an_image_just_below_2_31_bytes():
+    """The image's last bytes lie in a word across its end whose byte offset plus length does not fit
+    an int: at scale 1 the output is the image, and a constant image stays constant at any shrink (the
+    per-axis weights sum to one)."""
+    from paper_2608_27206_amd import pace
+    import torch
+    H, W = 49981, 14322
+    assert 2 ** 31 - 4 < 3 * H * W < 2 ** 31 and 3 * H * W % 4
+    say(f"resize {H}x{W}")
+    img = torch.empty(H, W, 3, dtype=torch.uint8, device="cuda").random_(1, 256)
+    assert torch.equal(pace.apc_downsample(img, H, W), img)
+    img.fill_(200)
+    for oh, ow in ((H // 3 + 1, W // 3 + 1), (H // 8, W // 8)):
+        out = pace.apc_downsample(img, oh, ow)
+        assert int(out.min()) == int(out.max()) == 200, (oh, ow, out[-1, -1])
 
 
 @pytest.mark.parametrize("case", range(6))
