@@ -36,12 +36,10 @@ __device__ __forceinline__ uint32_t pack2(float a, float b) {   // two bf16, nea
   const f32x2 v = {a, b};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
-// x / (1 + exp(-x)) on the exponential and reciprocal units: within 2^-20 of the value, which the
-// bf16 rounding that follows (2^-9) hides; with expf and a division the 64 of a lane cost as much
-// as a tenth of the product
-__device__ __forceinline__ float silu(float x) {
-  return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(x * -1.4426950408889634f));
-}
+// expf and the division to a rounding each: on the exponential and reciprocal units alone the
+// error is 2^-18 at gates below -20 (the rounded product with log2 e), for 716 against 782 us of 42,196 x
+// 6,848 x 1,280.
+__device__ __forceinline__ float silu(float x) { return x / (1.0f + expf(-x)); }
 
 // ---------------------------------------------------------------- patchify
 // One thread per 16-byte chunk of X: eight neighbouring bytes of a patch row in one load, byte by
@@ -95,7 +93,7 @@ __global__ __launch_bounds__(256) void preview_patchify(const uint8_t* __restric
 // 1.6 GHz; at K = 1,280 47%, since a tile's first loads and the burst of stores (and residual
 // loads) at the end of a round take a third of its time.  Measured against the 128 x 128
 // register-staged kernel before it, 42,196 rows: N = K = 1,280 with residual 337 -> 197 us; N =
-// 6,848, K = 1,280 with SwiGLU 1,211 -> 712 us (1,038 TFLOP/s); N = 1,280, K = 3,424 with residual
+// 6,848, K = 1,280 with SwiGLU 1,211 -> 782 us (946 TFLOP/s); N = 1,280, K = 3,424 with residual
 // 661 -> 401 us; 8,192^3 1,590 -> 868 us (1,267 TFLOP/s).  Stages of 32 in a ring of four: 205, 744, 446
 // and 920 us.  Tried with stages of 32, TFLOP/s at 8,192^3 against 1,169: 4 x 4 MFMA tiles per wave
 // with four waves 1,080 (one wave per SIMD does not hide its own LDS reads), two 128 x 256

@@ -51,6 +51,29 @@ def test_gemm_epilogues(M, N, K, epi):
     assert np.all(np.abs(got - ref) <= tol), float(np.max(np.abs(got - ref) - tol))
 
 
+def test_swiglu_in_single_precision():
+    """SiLU(gate) up to 2^-21: expf's 2^-23, and 2^-24 each for 1 + e, the division and the product come to
+    5 x 2^-24.  The products are zero, so gate and up are the fp32 biases; up puts each result 2^-21 to
+    either side of the middle between two bf16 values, and the right one of the two has to come out."""
+    from paper_2608_27206_amd import pace
+    import torch
+    rs = np.random.default_rng(5)
+    n = 8192
+    gate = np.concatenate([rs.uniform(-80, 20, n - 64), rs.normal(0, 1, 64)]).astype(np.float32)
+    silu = gate.astype(np.float64) / (1.0 + np.exp(-gate.astype(np.float64)))
+    mid = 1.0 + (2 * rs.integers(0, 128, n) + 1) * 2.0 ** -8
+    side = np.where(np.arange(n) % 2 == 0, 1.0, -1.0)
+    up = (mid * (1.0 + side * 1.2 * 2.0 ** -21) / np.abs(silu)).astype(np.float32)
+    val = np.abs(silu) * up.astype(np.float64)
+    ok = (np.abs(val / mid - 1.0) >= 2.0 ** -21) & (np.sign(val - mid) == side) & np.isfinite(up)
+    assert ok.mean() > 0.99   # up's own rounding moves few of them closer
+    bias = np.stack([gate, up], 1).reshape(-1)
+    a, b = np.zeros((3, 8), np.uint16), np.zeros((2 * n, 8), np.uint16)
+    got = host_bf16_to_f64(pace.gemm_bf16(dev_bf16(a), dev_bf16(b), torch.from_numpy(bias).cuda(), None, 2))
+    want = np.sign(silu) * (mid + side * 2.0 ** -8)
+    assert np.array_equal(got[:, ok], np.broadcast_to(want[ok], got[:, ok].shape)), np.mean(got[0, ok] != want[ok])
+
+
 def _block_case(H, W, seed=11):
     from paper_2608_27206_amd import pace
     import torch
