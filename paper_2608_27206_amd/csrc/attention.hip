@@ -278,6 +278,10 @@ __device__ __forceinline__ uint2 lds_read_tr16(const uint16_t* p) {
 // and the O accumulators are rescaled only when some row's max really moves.
 constexpr float kRescaleSlack = 8.0f;
 
+// What the exponentials subtract: a row whose scores are all -inf so far takes 0, so that its
+// probabilities and their sum are 0 and its LSE -inf.
+__device__ __forceinline__ float finite_max(float m) { return m == -INFINITY ? 0.f : m; }
+
 // The forward kernel.  Per 64-key tile t, every wave:
 //   - issues S^T(t+1) = K(t+1) Q^T on the MFMA pipe (K runs one tile ahead in LDS),
 //   - runs the online softmax of S^T(t) on the VALU while those MFMAs execute,
@@ -454,7 +458,7 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_fwd(const FwdParams
 
   // exp, row sum and bf16 packing of the tile in s, then O^T += V^T P^T (buffer BUF)
   auto exp_pv = [&](f32x16* s, int buf) __attribute__((always_inline)) {
-    const float m_off = (m_used == -INFINITY) ? 0.f : m_used;
+    const float m_off = finite_max(m_used);
     bf16x8 pb[2][2];
 #pragma unroll
     for (int st = 0; st < 2; ++st) {
@@ -575,8 +579,8 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_fwd(const FwdParams
     __syncthreads();
     if (grp == 1) return;   // group 0's four waves write the rows
     const float m1 = pv[(kPartV - 2) * 64], l1 = pv[(kPartV - 1) * 64];
-    const float m = fmaxf(m_used, m1);
-    const float f0 = fast_exp2(m_used - m), f1 = fast_exp2(m1 - m);
+    const float m = fmaxf(m_used, m1), m0 = finite_max(m);
+    const float f0 = fast_exp2(m_used - m0), f1 = fast_exp2(m1 - m0);
 #pragma unroll
     for (int t2 = 0; t2 < C::NT; ++t2)
 #pragma unroll
@@ -1105,7 +1109,7 @@ __global__ __launch_bounds__(kRotThreads, 1) void attn_fwd_rot(const FwdParams p
     __syncthreads();
     const float* mr = mx + wl * 32 + c32;
     const float m_all = fmaxf(fmaxf(mr[0], mr[kRotSplitBM]), mr[2 * kRotSplitBM]);
-    const float f = fast_exp2(m_used - m_all);            // 0 for a group without tiles
+    const float f = fast_exp2(m_used - finite_max(m_all));   // 0 for a group without tiles
     m_off = m_all - kP16Shift;
 #pragma unroll
     for (int t2 = 0; t2 < C::NT; ++t2)
@@ -1236,13 +1240,14 @@ __global__ __launch_bounds__(kWinThreads) void attn_window(const FwdParams p, fl
       mx = fmaxf(mx, s[st][r]);
     }
   mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * p.scale_log2;
+  const float m0 = finite_max(mx);
   float pv[2][16];
   float lp = 0.f;
 #pragma unroll
   for (int st = 0; st < 2; ++st)
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      pv[st][r] = fast_exp2(s[st][r] * p.scale_log2 - mx);
+      pv[st][r] = fast_exp2(s[st][r] * p.scale_log2 - m0);
       lp += pv[st][r];
     }
   const float l = lp + __shfl_xor(lp, 32, 64);

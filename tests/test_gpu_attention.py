@@ -270,6 +270,49 @@ def test_vit_long_segment_splits_d80(H, sizes):
     np.testing.assert_allclose(mass.sum(1), n, rtol=1e-4)
 
 
+@pytest.mark.parametrize("d,causal,sizes", [(80, False, [64, 9]), (128, False, [64, 9]), (80, False, [100]),
+                                            (80, False, [900]), (128, False, [900, 65]), (80, False, [1024]),
+                                            (80, False, [1153, 64]), (80, False, [1024] * 40), (128, True, [900, 65]),
+                                            (80, True, [900]), (128, True, [300])])
+def test_rows_without_a_finite_score(d, causal, sizes):
+    """Every form of the forward (windows, one and two key groups, rows or keys split): a head whose
+    scores are all -inf has LSE -inf in every row; where only every third key tile is, the rows are those
+    over the other keys."""
+    from paper_2608_27206_amd import pace
+    import torch
+    cu = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    n = int(cu[-1])
+    q, k, v = (wl.bf16_bits_to_f64(x) for x in _vit_case(211, cu, 2, d))
+    q = np.abs(q) + 0.125
+    k[:, 0] = -np.inf
+    j = np.concatenate([np.arange(x) for x in sizes])
+    k[(j // 64 % 3 == 1) | (j == 5), 1] = -np.inf
+    bits = [wl.f32_to_bf16_bits(x.astype(np.float32)) for x in (q, k, v)]
+    q = wl.bf16_bits_to_f64(bits[0])
+    say(f"rows without a finite score d={d} causal={causal} sizes={sizes[:4]}")
+    dq, dk, dv = (dev_bf16(x) for x in bits)
+    if causal:
+        z = dev_i32([0] * (len(sizes) + 1))
+        o, lse, _ = pace.prefill_attention_with_mass(dq, dk, dv, dev_i32(cu), max(sizes), z, z, 0, 0, z, z, 0,
+                                                     want_mass=False)
+    else:
+        o, lse, _ = pace.vit_attention(dq, dk, dv, dev_i32(cu), max(sizes), want_mass=False)
+    torch.cuda.synchronize()
+    assert np.all(host(lse)[0] == -np.inf)
+    o, lse = host_bf16_to_f64(o)[:, 1], host(lse)[1]
+    with np.errstate(invalid="ignore"):
+        for a, b in list(zip(cu[:-1], cu[1:]))[:3]:
+            S = q[a:b, 1] @ np.where(np.isinf(k[a:b, 1]), 0.0, k[a:b, 1]).T / math.sqrt(d)
+            S[:, np.isinf(k[a:b, 1, 0])] = -np.inf
+            if causal:
+                S[np.triu_indices(b - a, 1)] = -np.inf
+            m = S.max(1, keepdims=True)
+            P = np.exp(S - m)
+            L = (m + np.log(P.sum(1, keepdims=True)))[:, 0]
+            assert np.max(np.abs(lse[a:b] - L)) <= LSE_TOL
+            assert np.max(np.abs(o[a:b] - P @ v[a:b, 1] / P.sum(1, keepdims=True))) <= O_TOL
+
+
 @pytest.mark.parametrize("d,hq,hkv,vis,text", [(128, 4, 2, [700, 0, 1], [100, 1, 63]), (80, 4, 1, [768], [1]),
                                                (128, 28, 4, [1600], [64]), (128, 28, 4, [1700], [64]),
                                                (128, 6, 3, [64, 900], [0, 3])])
