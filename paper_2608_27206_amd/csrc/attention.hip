@@ -226,6 +226,18 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 // ---------------------------------------------------------------- forward
+// Division of 0 <= n < 2^31 by d: n m >> s with m = ceil(2^s / d), s = 31 + ceil(log2 d), whose error
+// stays below n / 2^31 / d (Granlund and Montgomery).  A division by a kernel argument takes about 40
+// instructions.
+struct FastDiv { uint32_t m; int s; };
+inline FastDiv fast_div(int d) {
+  const int l = d <= 1 ? 0 : 32 - __builtin_clz(static_cast<unsigned>(d - 1));
+  return {static_cast<uint32_t>(((1ull << (31 + l)) + d - 1) / d), 31 + l};
+}
+__device__ __forceinline__ int div_fast(int n, FastDiv f) {
+  return static_cast<int>((static_cast<uint64_t>(static_cast<uint32_t>(n)) * f.m) >> f.s);
+}
+
 struct FwdParams {
   const uint16_t* q;
   const uint16_t* k;
@@ -235,7 +247,14 @@ struct FwdParams {
   const int32_t* cu;       // [nseg + 1]
   int Ntot, Hq, Hkv, group;
   int nseg, nqt;           // q tiles per segment in the grid
-  int xcd_classes;         // gcd(Hkv, 8): classes of KV heads that own XCDs (causal order)
+  // causal order (see attn_fwd and causal_order)
+  int xcd_classes;         // gcd(Hkv, 8): classes of KV heads that own XCDs
+  int heads;               // query heads of a class
+  int seg_group;           // segments taken together
+  int rotate;              // the segments change places from level to level
+  FastDiv by_group_all;    // workgroups of seg_group segments
+  FastDiv by_level[2];     // those of one query tile index: of seg_group segments, of the last ones
+  FastDiv by_heads, by_group;
   float scale_log2;        // scale * log2(e)
   const uint16_t* vt;      // fp16 V^T tiles (rotation kernel only)
   long long vt_cols;
@@ -290,7 +309,7 @@ __device__ __forceinline__ float finite_max(float m) { return m == -INFINITY ? 0
 // transposing LDS reads whose source addresses also apply the key permutation that
 // matches the accumulator layout of P^T: A slot (g, 4*rd + j) holds key 8*rd + 4*g + j of
 // each 16-key chunk.
-// With GROUPS = 2 (small grids: see fwd_groups) two groups of four waves work on the same 128
+// With GROUPS = 2 (small grids: see launch_fwd) two groups of four waves work on the same 128
 // rows, taking every second key tile each with K and V buffers of their own; their partial O^T,
 // row maxima and row sums are combined at the end.
 template <int D, bool CAUSAL, int GROUPS>
@@ -302,22 +321,42 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_fwd(const FwdParams
   int h, seg, qt;
   if (CAUSAL) {
     // Longest rows first on every XCD: workgroup b goes to XCD b % 8, and slot by slot each XCD
-    // takes the query tiles from the last to the first, all its heads and segments of one
-    // tile index together.  The KV heads of class c = kvh % g, g = gcd(Hkv, 8), belong to 8 / g
+    // takes the query tiles from the last to the first, all its heads and the segments of a group
+    // of one tile index together.  The KV heads of class c = kvh % g, g = gcd(Hkv, 8), belong to 8 / g
     // XCDs, which take turns, so that the query heads of a KV head still share L2s.  (In one
     // head after the other an XCD ended on the long rows of a head that it shares with the next
     // XCD: 510 tile times against a mean of 418 in a list schedule of the 4K prefill's 28 heads
     // over 84 query tiles, 434 in this order.  Measured: the 4K prefill with its text mass 875 ->
     // 781 us, 1,183 tokens 32.2 -> 26.7 us.)
-    const int xpc = kNumXcd / p.xcd_classes;
+    const int lx = __builtin_ctz(kNumXcd / p.xcd_classes);   // log2 of a class's XCDs
     const int xcd = blockIdx.x % kNumXcd, slot = blockIdx.x / kNumXcd;
-    const int c = xcd / xpc, pos = slot * xpc + (xcd - c * xpc);
-    const int heads = p.Hq / p.xcd_classes, m = p.nseg * heads;
-    const int level = pos / m, rem = pos - level * m;
+    const int c = xcd >> lx;
+    int pos = (slot << lx) + (xcd - (c << lx));
+    int first = 0, nseg = p.nseg, last = 0;   // the group's segments
+    if (p.seg_group < p.nseg) {
+      const int sg = div_fast(pos, p.by_group_all);
+      first = sg * p.seg_group;
+      if (first >= p.nseg) return;
+      pos -= first * p.heads * p.nqt;
+      last = first + p.seg_group > p.nseg;
+      nseg = last ? p.nseg - first : p.seg_group;
+    }
+    const int level = div_fast(pos, p.by_level[last]);
     if (level >= p.nqt) return;
+    const int rem = pos - level * nseg * p.heads;
     qt = p.nqt - 1 - level;
-    seg = rem / heads;
-    const int hh = rem - seg * heads, kk = hh / p.group;
+    const int sl = div_fast(rem, p.by_heads);
+    // The workgroups of an XCD go to its four shader engines in turn.  Where the number of segments is
+    // even, those of one segment would come to the same one or two in every level, and a long
+    // segment among short ones to a quarter or half of the CUs: the segments move on by one every
+    // level or two (8 / 2 heads, 4,064 tokens beside three of 164: 135 -> 62 us, beside two 61).
+    int sr = sl;
+    if (p.rotate) {
+      sr += (nseg & 3) == 0 ? level & 3 : (nseg & 1) == 0 ? (level >> 1) & 1 : 0;
+      if (sr >= nseg) sr -= nseg;
+    }
+    seg = first + sr;
+    const int hh = rem - sl * p.heads, kk = div_fast(hh, p.by_group);
     h = (kk * p.xcd_classes + c) * p.group + (hh - kk * p.group);
   } else {
     const int lb = remap_block_id(blockIdx.x, gridDim.x);
@@ -1688,9 +1727,40 @@ inline bool rot_split(int N, int nseg, int max_seglen, int H) {
 // (16) 11.2 / 13.0, 600 (40) 15.1 / 15.1.  Without a mask all workgroups are long, so they
 // have to fit one per CU: 16 heads, 1,000 patches (128) 17.1 / 15.7, segments of 900, 800 and 700
 // (336) 22.9 / 26.3.
-inline int fwd_groups(const FwdParams& fp, bool causal, int max_seglen) {
+template <int D, bool CAUSAL>
+void launch_fwd(const FwdParams& fp, int max_seglen, dim3 grid, hipStream_t stream) {
   const long long wgs = blocks_bound(fp.Ntot, fp.nseg, max_seglen, kBM) * fp.Hq;
-  return max_seglen >= 768 && wgs <= (causal ? 384 : 256) ? 2 : 1;
+  if (max_seglen >= 768 && wgs <= (CAUSAL ? 384 : 256))
+    hipLaunchKernelGGL((attn_fwd<D, CAUSAL, 2>), grid, dim3(2 * kThreads), 0, stream, fp);
+  else
+    hipLaunchKernelGGL((attn_fwd<D, CAUSAL, 1>), grid, dim3(kThreads), 0, stream, fp);
+}
+
+// The order of the causal forward's workgroups (see attn_fwd).  Segments are taken together in groups of
+// so many that an XCD works on about eight K/V streams at a time: beyond that its workgroups of one
+// stream lie too far apart to share it in L2 (16 sequences of 4,128 tokens, 16 / 16 heads, two KV heads per
+// XCD: all at once 1,330 us, eight sequences 1,172, four 1,121).  But no fewer than about four rounds of
+// workgroups, of which the long rows of the last group would otherwise be a large part.
+inline void causal_order(FwdParams& fp, int max_seglen) {
+  fp.xcd_classes = fp.Hkv % 8 == 0 ? 8 : fp.Hkv % 4 == 0 ? 4 : fp.Hkv % 2 == 0 ? 2 : 1;
+  fp.heads = fp.Hq / fp.xcd_classes;
+  // if there are shorter segments, and a segment keeps its XCDs then
+  fp.rotate = static_cast<long long>(fp.nseg) * max_seglen > fp.Ntot && fp.heads % (kNumXcd / fp.xcd_classes) == 0;
+  constexpr int kStreams = 4, kLeastWgs = 768;
+  const int kvh = fp.Hkv / fp.xcd_classes;
+  const long long per_seg = static_cast<long long>(fp.Hq) * fp.nqt;
+  const long long least = (kLeastWgs + per_seg - 1) / per_seg;
+  const long long size = least > kStreams / kvh ? least : kStreams / kvh > 0 ? kStreams / kvh : 1;
+  const int groups = size < fp.nseg ? fp.nseg / static_cast<int>(size) : 1;   // of even sizes
+  fp.seg_group = (fp.nseg + groups - 1) / groups;
+  fp.by_level[0] = fast_div(fp.seg_group * fp.heads);
+  if (groups > 1) {
+    const int rest = fp.nseg % fp.seg_group;
+    fp.by_group_all = fast_div(fp.seg_group * fp.heads * fp.nqt);
+    fp.by_level[1] = fast_div((rest ? rest : fp.seg_group) * fp.heads);
+  }
+  fp.by_heads = fast_div(fp.heads);
+  fp.by_group = fast_div(fp.group);
 }
 
 template <int D>
@@ -1729,13 +1799,10 @@ pace_status_t launch_attention(FwdParams fp, bool causal, int max_seglen, const 
   }
   if (causal) {
     fp.nqt = (max_seglen + kBM - 1) / kBM;
-    fp.xcd_classes = fp.Hkv % 8 == 0 ? 8 : fp.Hkv % 4 == 0 ? 4 : fp.Hkv % 2 == 0 ? 2 : 1;
-    const int xpc = kNumXcd / fp.xcd_classes, per_class = fp.nqt * fp.nseg * (fp.Hq / fp.xcd_classes);
+    causal_order(fp, max_seglen);
+    const int xpc = kNumXcd / fp.xcd_classes, per_class = fp.nqt * fp.nseg * fp.heads;
     const dim3 grid(static_cast<unsigned>((per_class + xpc - 1) / xpc) * kNumXcd);
-    if (fwd_groups(fp, true, max_seglen) == 2)
-      hipLaunchKernelGGL((attn_fwd<D, true, 2>), grid, dim3(2 * kThreads), 0, stream, fp);
-    else
-      hipLaunchKernelGGL((attn_fwd<D, true, 1>), grid, dim3(kThreads), 0, stream, fp);
+    launch_fwd<D, true>(fp, max_seglen, grid, stream);
   } else if (D == 80 && max_seglen >= kRotMinSeg) {
     VtParams vp{};
     vp.v = fp.v; vp.vt = const_cast<uint16_t*>(fp.vt); vp.amax = const_cast<uint32_t*>(fp.vt_amax);
@@ -1767,10 +1834,7 @@ pace_status_t launch_attention(FwdParams fp, bool causal, int max_seglen, const 
   } else {
     fp.nqt = (max_seglen + kBM - 1) / kBM;
     const dim3 grid(fp.nqt * fp.nseg * fp.Hq);
-    if (fwd_groups(fp, false, max_seglen) == 2)
-      hipLaunchKernelGGL((attn_fwd<D, false, 2>), grid, dim3(2 * kThreads), 0, stream, fp);
-    else
-      hipLaunchKernelGGL((attn_fwd<D, false, 1>), grid, dim3(kThreads), 0, stream, fp);
+    launch_fwd<D, false>(fp, max_seglen, grid, stream);
   }
   pace_status_t st = check_launch("attn_fwd");
   if (st != PACE_OK || mp == nullptr || nmass == 0) return st;

@@ -340,6 +340,35 @@ def test_prefill_key_groups(d, hq, hkv, vis, text):
     assert err <= 0, f"mass rel err {rel}"
 
 
+@pytest.mark.parametrize("d,hq,hkv,seqs", [(128, 8, 8, [300, 129, 0, 64]), (80, 16, 16, [260, 1]),
+                                           (128, 16, 8, [130, 400]), (128, 8, 2, [520, 20, 1, 130]),
+                                           (128, 8, 2, [300, 20]), (80, 12, 3, [200, 0, 129]),
+                                           (128, 2, 2, [64] * 6), (128, 16, 16, [1 + 37 * i % 200 for i in range(49)]),
+                                           (80, 8, 8, [1 + 53 * i % 256 for i in range(98)])])
+def test_prefill_workgroup_order(d, hq, hkv, seqs):
+    """The causal forward's order of workgroups covers every query tile of every head: KV heads in eight
+    classes (one XCD each) with one and several query heads per KV head, and in one, two and eight; segments
+    that change places from level to level (an even number of unequal length) and that do not; more
+    segments than a group takes (49 in groups of 25 and 24, 98 in groups of 49)."""
+    from paper_2608_27206_amd import pace
+    import torch
+    cu = np.concatenate([[0], np.cumsum(seqs)]).astype(np.int32)
+    n = int(cu[-1])
+    q, k, v = (wl.random_bf16(191 + i, (n, h, d)) for i, h in enumerate((hq, hkv, hkv)))
+    say(f"prefill order d={d} heads={hq}/{hkv} sequences={seqs[:6]} of {len(seqs)}")
+    z = dev_i32([0] * (len(seqs) + 1))
+    dq = dev_bf16(q)
+    o, lse = torch.full_like(dq, float("nan")), torch.full((hq, n), float("nan"), device="cuda")
+    pace.prefill_attention_with_mass(dq, dev_bf16(k), dev_bf16(v), dev_i32(cu), max(seqs), z, z, 0, 0, z, z, 0,
+                                     want_mass=False, o=o, lse=lse)
+    torch.cuda.synchronize()
+    none = [0] * len(seqs)
+    Or, Lr, _ = oatt.prefill_attention(wl.bf16_bits_to_f64(q), wl.bf16_bits_to_f64(k), wl.bf16_bits_to_f64(v), cu,
+                                       none, none, none, 1 / math.sqrt(d))
+    assert np.max(np.abs(host_bf16_to_f64(o) - Or)) <= O_TOL
+    assert np.max(np.abs(host(lse) - Lr)) <= LSE_TOL
+
+
 def test_prefill_tiny_config():
     w = wl.make_workload(0)
     mass, Mr = _check_prefill(w.prefill)
