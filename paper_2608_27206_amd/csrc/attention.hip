@@ -312,7 +312,7 @@ __device__ __forceinline__ float finite_max(float m) { return m == -INFINITY ? 0
 // With GROUPS = 2 (small grids: see launch_fwd) two groups of four waves work on the same 128
 // rows, taking every second key tile each with K and V buffers of their own; their partial O^T,
 // row maxima and row sums are combined at the end.
-template <int D, bool CAUSAL, int GROUPS>
+template <int D, bool CAUSAL, int GROUPS, bool PRIO>
 __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_fwd(const FwdParams p) {
   using C = FwdCfg<D>;
   __shared__ __align__(16) uint16_t Ksm[GROUPS][2][kBN * C::KS];
@@ -555,9 +555,8 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_fwd(const FwdParams
     if (has_next) load_v(tile_of(t + 1), buf ^ 1);
     tile_max(s_cur, tile_of(t) * kBN);
     if constexpr (has_next) {
-      // the matrix work of this wave before the maximum of the other one on the SIMD (4K prefill
-      // 797 -> 785 us with its text mass)
-      __builtin_amdgcn_s_setprio(1);
+      // the matrix work of this wave before the maximum of the other one on the SIMD
+      if constexpr (PRIO) __builtin_amdgcn_s_setprio(1);
       qk(buf ^ 1, s_next);
       exp_pv(s_cur, buf);
       // request: LDS reads issued a few MFMAs ahead of their use; every MFMA followed by a
@@ -574,7 +573,7 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_fwd(const FwdParams
         __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
         __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
       });
-      __builtin_amdgcn_s_setprio(0);
+      if constexpr (PRIO) __builtin_amdgcn_s_setprio(0);
     } else {
       exp_pv(s_cur, buf);
     }
@@ -1727,13 +1726,24 @@ inline bool rot_split(int N, int nseg, int max_seglen, int H) {
 // (16) 11.2 / 13.0, 600 (40) 15.1 / 15.1.  Without a mask all workgroups are long, so they
 // have to fit one per CU: 16 heads, 1,000 patches (128) 17.1 / 15.7, segments of 900, 800 and 700
 // (336) 22.9 / 26.3.
+//
+// One group's waves take turns by priority (PRIO) where their workgroups share CUs for a while.  Without
+// and with s_setprio around the matrix work, us: prefill at 28 / 4 heads, 2,328 tokens (532 workgroups) 52.1 /
+// 53.5, 2,728 (616) 63.8 / 65.4, 3,328 (728) 84.5 / 84.2, 4,328 (952) 141.5 / 127.6, 9,128 (2,016) 544 / 526, 10,677
+// with its text mass 767 / 749; at 8 / 2 heads, 9,128 (576) 188.7 / 195.2; two key groups take 1-2% longer with
+// it.  Without a mask the rows are all long: 28 heads of 128, 1,500 patches (336) 48.5 / 43.9, 16 heads, 3,000
+// (384) 86.7 / 77.5, 8 heads, 9,000 (568) 393 / 400.  Rows of few key tiles: 16 segments of 500 patches, 16 heads
+// (1,024) 43.8 / 45.6, 16 sequences of 328 tokens, 16 / 16 heads (768) 25.4 / 27.0; four of 828 at 28 / 4 heads (784)
+// 35.5 / 33.0, 16 of them (3,136) 119 / 121.
 template <int D, bool CAUSAL>
 void launch_fwd(const FwdParams& fp, int max_seglen, dim3 grid, hipStream_t stream) {
   const long long wgs = blocks_bound(fp.Ntot, fp.nseg, max_seglen, kBM) * fp.Hq;
   if (max_seglen >= 768 && wgs <= (CAUSAL ? 384 : 256))
-    hipLaunchKernelGGL((attn_fwd<D, CAUSAL, 2>), grid, dim3(2 * kThreads), 0, stream, fp);
+    hipLaunchKernelGGL((attn_fwd<D, CAUSAL, 2, false>), grid, dim3(2 * kThreads), 0, stream, fp);
+  else if (max_seglen >= 768 && (!CAUSAL || wgs > 620))
+    hipLaunchKernelGGL((attn_fwd<D, CAUSAL, 1, true>), grid, dim3(kThreads), 0, stream, fp);
   else
-    hipLaunchKernelGGL((attn_fwd<D, CAUSAL, 1>), grid, dim3(kThreads), 0, stream, fp);
+    hipLaunchKernelGGL((attn_fwd<D, CAUSAL, 1, false>), grid, dim3(kThreads), 0, stream, fp);
 }
 
 // The order of the causal forward's workgroups (see attn_fwd).  Segments are taken together in groups of
