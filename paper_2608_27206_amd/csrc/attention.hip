@@ -1776,11 +1776,12 @@ inline void causal_order(FwdParams& fp, int max_seglen) {
 template <int D>
 pace_status_t launch_mass(MassParams mp, int max_seglen, hipStream_t stream) {
   if constexpr (D == 80) {
-    // With fewer workgroups of 256 keys than CUs, the waves of a workgroup take the same 64 keys
-    // and split the query rows: 1,024, 2,048 and 3,000 patches x 16 heads 19.7, 32.3 and 44.4 us
-    // in 256 keys, 11.1, 21.8 and 39.8 us split; 4,096 (256 workgroups) 58.6 against 65.3; 42,196:
-    // 4,972 against 5,909 (each query tile serves a quarter of the keys).
-    if (blocks_bound(mp.Ntot, mp.nseg, max_seglen, kMassKeys) * mp.Hq < 256) {
+    // With up to 192 workgroups of 256 keys, the waves of a workgroup take the same 64 keys and
+    // split the query rows.  In 256 keys / split, us: 1,024, 2,048 and 3,000 patches x 16 heads (64, 128 and
+    // 192 workgroups) 16.1 / 9.1, 28.8 / 17.6 and 41.1 / 35.0, 3,200 (208) 43.4 / 45.7, 4,000 (256) 54.0 /
+    // 58.1; 12 heads, 4,096 (192) 55.0 / 47.1, 5,000 (240) 69.6 / 72.1; 8 heads, 6,000 (192) 79.1 / 64.7; 16
+    // heads, 42,196: 4,972 / 5,909 (each query tile serves a quarter of the keys).
+    if (blocks_bound(mp.Ntot, mp.nseg, max_seglen, kMassKeys) * mp.Hq <= 192) {
       mp.nkt = (max_seglen + kMassKeys / 4 - 1) / (kMassKeys / 4);
       hipLaunchKernelGGL((attn_mass<80, false, true>), dim3(mp.nkt * mp.nseg * mp.Hq), dim3(kThreads), 0, stream, mp);
       return check_launch("attn_mass");

@@ -9,7 +9,7 @@ import pytest
 
 from oracle import attention as oatt
 from paper_2608_27206_amd import workloads as wl
-from tests.gpu_util import (dev_bf16, dev_i32, host, host_bf16_to_f64, mass_ok, say)
+from tests.gpu_util import (dev_bf16, dev_i32, host, host_bf16_to_f64, mass_ok, oracle_mass_parallel, say)
 
 pytestmark = pytest.mark.gpu
 
@@ -249,11 +249,11 @@ def _check_prefill(p):
 @pytest.mark.parametrize("H,sizes", [(1, [1024]), (1, [1153, 1, 64, 65, 200]), (2, [1100, 0, 0, 129]), (16, [2048]),
                                      (2, [16200]), (16, [2049]), (3, [1500] + [0] * 3000)])
 def test_vit_long_segment_splits_d80(H, sizes):
-    """Both forms of the long-segment forward (its groups split the rows or the keys) and of the
-    mass pass (its waves split the keys or the query rows), around the sizes where they change:
-    segments of one and two key tiles beside a long one (groups without a tile), no rows at all,
-    the largest grid of the split forms and the one above; more empty segments than tokens (the
-    maxima of V then come from one block per segment)."""
+    """Both forms of the long-segment forward (its groups split the rows or the keys), around the
+    sizes where they change: segments of one and two key tiles beside a long one (groups without a
+    tile), no rows at all, the largest grid of the key split and the one above; more empty segments
+    than tokens (the maxima of V then come from one block per segment).  The mass pass splits the
+    query rows in all but the last of them (see test_vit_mass_split_d80)."""
     cu = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
     q, k, v = _vit_case(131 + H, cu, H, 80)
     if sizes[0] < 5000:
@@ -268,6 +268,24 @@ def test_vit_long_segment_splits_d80(H, sizes):
     assert np.max(np.abs(o[rows] - Or)) <= O_TOL
     assert np.max(np.abs(lse[:, rows] - Lr)) <= LSE_TOL
     np.testing.assert_allclose(mass.sum(1), n, rtol=1e-4)
+
+
+@pytest.mark.parametrize("H,sizes", [(16, [3072]), (16, [3073]), (4, [8000, 3000, 1000]), (4, [8000, 3000, 1600])])
+def test_vit_mass_split_d80(H, sizes):
+    """The mass pass on both sides of the line between its forms (the waves of a workgroup split the query
+    rows up to 192 workgroups of 256 keys, the keys above): every key's mass of the first and last head,
+    and of all heads that a segment's rows sum to one."""
+    cu = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    q, k, v = _vit_case(151 + H, cu, H, 80)
+    say(f"vit mass H={H} sizes={sizes}")
+    _, _, mass = _run_vit(q, k, v, cu, max(sizes))
+    qf, kf = wl.bf16_bits_to_f64(q), wl.bf16_bits_to_f64(k)
+    for a, b in zip(cu[:-1], cu[1:]):
+        np.testing.assert_allclose(mass[:, a:b].sum(1), b - a, rtol=1e-4)
+        for h in (0, H - 1):
+            ref = oracle_mass_parallel(qf[a:b, h], kf[a:b, h], False, 1 / math.sqrt(80), np.arange(b - a))
+            err, rel = mass_ok(mass[h, a:b], ref, b - a)
+            assert err <= 0, f"mass rel err {rel}"
 
 
 @pytest.mark.parametrize("d,causal,sizes", [(80, False, [64, 9]), (128, False, [64, 9]), (80, False, [100]),
