@@ -28,7 +28,6 @@ __device__ __forceinline__ uint16_t to_bf16(float f) {
   u += 0x7FFFu + ((u >> 16) & 1u);   // round to nearest even (finite values)
   return static_cast<uint16_t>(u >> 16);
 }
-__device__ __forceinline__ float from_bf16(uint16_t b) { return __uint_as_float(static_cast<uint32_t>(b) << 16); }
 
 __device__ __forceinline__ uint32_t pack2(float a, float b) {   // two bf16, nearest even
   typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -88,7 +87,10 @@ __global__ __launch_bounds__(256) void preview_patchify(const uint8_t* __restric
 //   The product is formed as C^T (B's rows are the MFMA's A operand): a lane then holds four
 // neighbouring columns of one row, which makes SwiGLU's gate and up neighbours in one lane; the
 // tile leaves through LDS so that rows are stored in 16-byte chunks, and a residual tile comes
-// the same way (read straight into the lanes it cost 20 us of a 64-us round of tiles).
+// the same way (read straight into the lanes it cost 20 us of a 64-us round of tiles).  Rows of other
+// alignments go in units of 8, 4 or 2 bytes, neighbouring lanes taking neighbouring units (a lane's
+// eight values one by one, and the residual by lane: 6,000 x 1,290 x 1,280 with residual 76.5 -> 56.3 us,
+// 20,000 x 2,564 x 640 151.6 -> 98.1).
 //   Bound: MFMA.  At 8,192^3 the matrix cores are busy 68% of the cycles and the clock falls to
 // 1.6 GHz; at K = 1,280 47%, since a tile's first loads and the burst of stores (and residual
 // loads) at the end of a round take a third of its time.  Measured against the 128 x 128
@@ -111,7 +113,8 @@ struct GemmParams {
   int M, N, K;
   int tiles_m, tiles_n;
   int mode;
-  int vec;                  // C (and R) rows are 16-byte aligned: stored in 16-byte chunks
+  int width;                // elements per access to C and R: 8, 4, 2 or 1 as their alignment allows
+  int res_dma;              // the residual tiles come by DMA (16-byte rows)
 };
 
 typedef __attribute__((address_space(3))) const char g_lds_char;
@@ -143,8 +146,23 @@ __device__ __forceinline__ void g_wait_lds() { asm volatile("s_waitcnt vmcnt(%0)
 // Workgroup barrier alone: the waits before it say what it orders.
 __device__ __forceinline__ void g_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
+// What an access to W neighbouring elements moves.
+template <int W> struct GemmUnit;
+template <> struct GemmUnit<8> { typedef uint4 type; };
+template <> struct GemmUnit<4> { typedef uint2 type; };
+template <> struct GemmUnit<2> { typedef uint32_t type; };
+template <> struct GemmUnit<1> { typedef uint16_t type; };
+// f with W = 8, 4, 2 or 1 as a constant
+template <typename F>
+__device__ __forceinline__ void with_width(int width, F f) {
+  if (width == 8) f(std::integral_constant<int, 8>{});
+  else if (width == 4) f(std::integral_constant<int, 4>{});
+  else if (width == 2) f(std::integral_constant<int, 2>{});
+  else f(std::integral_constant<int, 1>{});
+}
+
 template <int MI, int NI, int WM, int WN, int ST>
-__global__ __launch_bounds__(64 * WM * WN, MI * NI > 8 ? 1 : 2) void gemm_bf16_nt(const GemmParams p) {
+__global__ __launch_bounds__(64 * WM * WN, 2) void gemm_bf16_nt(const GemmParams p) {
   constexpr int BM = 32 * MI * WM, BN = 32 * NI * WN;
   constexpr int NW = WM * WN, kGThreads = 64 * NW;
   constexpr int kStage = (BM + BN) * kGK;            // elements per stage
@@ -280,8 +298,7 @@ __global__ __launch_bounds__(64 * WM * WN, MI * NI > 8 ? 1 : 2) void gemm_bf16_n
   const int mode = p.mode;
   const bool glu = mode == kEpiSwiglu;
   constexpr int kCh = BN / 8;
-  const bool res_lds = mode == kEpiResidual && p.vec;
-  if (res_lds) {
+  if (mode == kEpiResidual && p.res_dma) {
     constexpr int kRows = 512 / BN;   // tile rows per wave-wide DMA
     const gi32x4 rr = g_rsrc(p.R + static_cast<long long>(bm) * p.N, static_cast<unsigned>(min(BM, p.M - bm)) * p.N * 2u);
 #pragma unroll
@@ -291,6 +308,20 @@ __global__ __launch_bounds__(64 * WM * WN, MI * NI > 8 ? 1 : 2) void gemm_bf16_n
       g_dma16(rr, lds0 + i * 1024, n < p.N ? static_cast<unsigned>(r * p.N + n) * 2u : kGOut);
     }
     g_wait<0>();
+    __syncthreads();
+  } else if (mode == kEpiResidual) {
+    with_width(p.width, [&](auto WC) __attribute__((always_inline)) {
+      constexpr int W = decltype(WC)::value, kUnits = BN / W;
+      typedef typename GemmUnit<W>::type T;
+#pragma unroll 8
+      for (int c = tid; c < BM * kUnits; c += kGThreads) {
+        const int r = c / kUnits, cl = c % kUnits * W;
+        T v{};
+        if (bm + r < p.M && bn + cl < p.N)
+          v = *reinterpret_cast<const T*>(p.R + static_cast<long long>(bm + r) * p.N + bn + cl);
+        *reinterpret_cast<T*>(&lds[r * BN + (((cl >> 3) ^ (r & (kCh - 1))) << 3) + (cl & 7)]) = v;
+      }
+    });
     __syncthreads();
   }
   const auto rbias = range_rsrc(p.bias[z], p.bias[z] != nullptr ? static_cast<unsigned>(p.N) * 4u : 0u);
@@ -306,7 +337,7 @@ __global__ __launch_bounds__(64 * WM * WN, MI * NI > 8 ? 1 : 2) void gemm_bf16_n
   for (int j = 0; j < NI; ++j)
 #pragma unroll
     for (int jj = 0; jj < 4; ++jj) {
-      const int cl = wn + 32 * j + 8 * jj + 4 * g, n = bn + cl;
+      const int cl = wn + 32 * j + 8 * jj + 4 * g;
 #pragma unroll
       for (int i = 0; i < MI; ++i) {
         const int rl = wm + 32 * i + c32;
@@ -319,15 +350,10 @@ __global__ __launch_bounds__(64 * WM * WN, MI * NI > 8 ? 1 : 2) void gemm_bf16_n
               pack2(silu(v[0]) * v[1], silu(v[2]) * v[3]);
         } else {
           uint2* at = reinterpret_cast<uint2*>(&lds[rl * BN + (((cl >> 3) ^ (rl & (kCh - 1))) << 3) + (cl & 7)]);
-          if (res_lds) {
+          if (mode == kEpiResidual) {
             const uint2 u = *at;
             v[0] += __uint_as_float(u.x << 16); v[1] += __uint_as_float(u.x & 0xffff0000u);
             v[2] += __uint_as_float(u.y << 16); v[3] += __uint_as_float(u.y & 0xffff0000u);
-          } else if (mode == kEpiResidual && bm + rl < p.M) {
-            const uint16_t* r = p.R + static_cast<long long>(bm + rl) * p.N + n;
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-              if (n + q < p.N) v[q] += from_bf16(r[q]);
           }
           *at = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
         }
@@ -337,18 +363,18 @@ __global__ __launch_bounds__(64 * WM * WN, MI * NI > 8 ? 1 : 2) void gemm_bf16_n
   const int nc = glu ? p.N / 2 : p.N, n0 = glu ? bn / 2 : bn;   // columns of C, the tile's first
   const int cpr = glu ? kCh / 2 : kCh, cbits = __builtin_ctz(cpr);
   uint16_t* C = p.C[z];
-  for (int c = tid; c < BM * cpr; c += kGThreads) {
-    const int r = c >> cbits, ch = c & (cpr - 1);
-    const int m = bm + r, n = n0 + ch * 8;
-    if (m >= p.M || n >= nc) continue;
-    uint16_t* dst = C + static_cast<long long>(m) * nc + n;
-    const uint16_t* src = &lds[(r * cpr + (ch ^ (r & (cpr - 1)))) * 8];
-    if (p.vec) {
-      *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(src);
-    } else {
-      for (int q = 0; q < 8 && n + q < nc; ++q) dst[q] = src[q];
+  with_width(p.width, [&](auto WC) __attribute__((always_inline)) {
+    constexpr int W = decltype(WC)::value, kLog = W == 8 ? 0 : W == 4 ? 1 : W == 2 ? 2 : 3;   // log2 of 8 / W
+    typedef typename GemmUnit<W>::type T;
+    const int ubits = cbits + kLog;
+    for (int c = tid; c < BM << ubits; c += kGThreads) {
+      const int r = c >> ubits, u = c & ((1 << ubits) - 1), ch = u >> kLog;
+      const int m = bm + r, n = n0 + u * W;
+      if (m >= p.M || n >= nc) continue;
+      *reinterpret_cast<T*>(C + static_cast<long long>(m) * nc + n) =
+          *reinterpret_cast<const T*>(&lds[(r * cpr + (ch ^ (r & (cpr - 1)))) * 8 + (u & (8 / W - 1)) * W]);
     }
-  }
+  });
 }
 
 // ---------------------------------------------------------------- RMSNorm
@@ -410,20 +436,29 @@ void launch_tile(GemmParams p, int nz, hipStream_t stream) {
 }
 
 // Tiles of 256 x 256 (one workgroup per CU) use the matrix cores best, but come in rounds of 256;
-// tiles of 64 x 128 fill the chip from small products on.  On 42,196 x 1,280 x 1,280 the large
-// tiles ran 4 rounds of 52 us at 640 TFLOP/s against 452 TFLOP/s with the small ones (both with
-// stages of 32); on 1,024 x 1,280 x 1,280 (20 large tiles) 32.5 us against 12.3.  So one round of large tiles costs
-// as much as about 156 of them in small ones, and a launch of small ones at least 0.3 of a round.
-// The rows go to whichever of these is the shortest: large tiles alone, small ones alone, or the
-// full rounds in large and the remaining rows in small tiles.
+// tiles of 64 x 128 fill the chip from small products on.  With stages of 64, 42,196 x 1,280 x 1,280 takes 168 us
+// in large tiles (four rounds of 42) and 215 in small ones (825 large tiles' area): a round costs as much
+// as about 156 large tiles in small ones.  A launch of small tiles costs at least 0.3 of a round (11.6
+// us at 1,024 rows).  The rows go to whichever of these is the shortest: large tiles alone, small ones alone,
+// or the full rounds in large and the remaining rows in small tiles; large ones alone also if they
+// cost 0.15 more (20,000 rows: two rounds 78.3 us, one and 0.9 of one in small tiles 84.3, as the second
+// launch starts in the first one's idle end), and two launches only if they cost 0.1 less.  Over 149
+// products (1 to 42,196 rows; N = 100 to 6,854; K = 592 to 3,424) the choice is within 6% of the best of
+// the three.
 pace_status_t launch_gemm(GemmParams p, int nz, hipStream_t stream) {
   const int nc = p.mode == kEpiSwiglu ? p.N / 2 : p.N;
-  p.vec = nc % 8 == 0 && p.N < (1 << 20);   // a tile's rows of C and R within one buffer's range
-  for (int z = 0; z < nz; ++z) p.vec = p.vec && aligned16(p.C[z]);
-  if (p.mode == kEpiResidual) p.vec = p.vec && aligned16(p.R);
+  uintptr_t bits = 2 * static_cast<uintptr_t>(nc);
+  for (int z = 0; z < nz; ++z) bits |= reinterpret_cast<uintptr_t>(p.C[z]);
+  if (p.mode == kEpiResidual) bits |= reinterpret_cast<uintptr_t>(p.R);
+  p.width = bits % 16 == 0 ? 8 : bits % 8 == 0 ? 4 : bits % 4 == 0 ? 2 : 1;
+  p.res_dma = p.width == 8 && p.N < (1 << 20);   // a tile's rows of R within one buffer's range
   const long long rows = (p.M + 255) / 256, per_row = ((p.N + 255) / 256) * static_cast<long long>(nz);
-  auto small_cost = [&](long long r) { return r <= 0 ? 0.0 : fmax(0.3, static_cast<double>(r * per_row) / 156.0); };
-  auto cost = [&](long long r) { return static_cast<double>((r * per_row + 255) / 256) + small_cost(rows - r); };
+  const long long small_cols = ((p.N + 127) / 128) * static_cast<long long>(nz);
+  auto small_cost = [&](long long r) {   // of the rows from 256 r on; eight small tiles cover a large one
+    const long long t = (p.M - 256 * r + 63) / 64 * small_cols;
+    return t <= 0 ? 0.0 : fmax(0.3, static_cast<double>(t) / (8 * 156.0));
+  };
+  auto cost = [&](long long r) { return static_cast<double>((r * per_row + 255) / 256) + small_cost(r); };
   const long long full = rows * per_row / 256 * 256 / per_row;   // row tiles in full rounds
   long long best = 0;
   if (cost(full) + 0.1 < cost(best)) best = full;

@@ -51,6 +51,58 @@ def test_gemm_epilogues(M, N, K, epi):
     assert np.all(np.abs(got - ref) <= tol), float(np.max(np.abs(got - ref) - tol))
 
 
+def _sampled_gemm(M, N, K, epi, rows, c_off=0, r_off=0, in_place=False):
+    """Rows `rows` of a product against float64; C and the residual start c_off and r_off elements
+    past a 16-byte boundary, and nothing around C is written."""
+    from paper_2608_27206_amd import pace
+    import torch
+    say(f"gemm M={M} N={N} K={K} epilogue={epi} offsets {c_off} {r_off}")
+    gen = torch.Generator(device="cuda").manual_seed(M + 3 * N + K)
+    nc = N // 2 if epi == 2 else N
+    normal = lambda *s: torch.randn(*s, generator=gen, device="cuda")   # noqa: E731
+    a, b, bias = normal(M, K).bfloat16(), (normal(N, K) / K ** 0.5).bfloat16(), 0.1 * normal(N)
+    res = normal(M * N + 16).bfloat16()[r_off:r_off + M * N].view(M, N) if epi == 1 else None
+    buf = torch.full((M * nc + 32,), 7.0, dtype=torch.bfloat16, device="cuda")
+    out = buf[8 + c_off:8 + c_off + M * nc].view(M, nc)
+    rows = np.unique(np.clip(np.asarray(rows), 0, M - 1))
+    sel = torch.from_numpy(rows).cuda()
+    r64 = host_bf16_to_f64(res[sel]) if epi == 1 else 0.0
+    if in_place:
+        out.copy_(res)
+        res = out
+    pace.gemm_bf16(a, b, bias, res, epi, out=out)
+    torch.cuda.synchronize()
+    assert torch.all(buf[:8 + c_off] == 7.0) and torch.all(buf[8 + c_off + M * nc:] == 7.0)
+    ref = host_bf16_to_f64(a[sel]) @ host_bf16_to_f64(b).T + host(bias).astype(np.float64)[None, :] + r64
+    if epi == 2:
+        ref = _silu(ref[:, 0::2]) * ref[:, 1::2]
+    got = host_bf16_to_f64(out[sel])
+    tol = 2.0 ** -8 * np.abs(ref) + 1e-3 * np.sqrt(np.mean(ref ** 2))
+    assert np.all(np.abs(got - ref) <= tol), float(np.max(np.abs(got - ref) - tol))
+
+
+@pytest.mark.parametrize("M,N,K,epi", [(10500, 1280, 200, 0), (10300, 1280, 136, 1), (15460, 1280, 592, 1),
+                                       (10241, 1280, 1288, 2), (15460, 1284, 328, 2)])
+def test_gemm_large_tiles_over_many_stages(M, N, K, epi):
+    """The 256 x 256 tiles with K in more stages than their ring holds (even and odd numbers, tails of 8 to
+    48 values), alone and with the remaining rows in small tiles: rows at both ends of the tiles, at
+    the line between the two and at the end."""
+    ends = np.concatenate([np.arange(0, M, 256), np.arange(255, M, 256), np.arange(128, M, 512)])
+    _sampled_gemm(M, N, K, epi, np.concatenate([ends, np.arange(13050, 13060), np.arange(M - 66, M)]))
+
+
+@pytest.mark.parametrize("N,c_off,r_off,width", [(264, 0, 0, 8), (264, 4, 0, 4), (264, 0, 4, 4), (268, 0, 0, 4),
+                                                 (268, 2, 4, 2), (270, 0, 0, 2), (270, 0, 1, 1), (271, 0, 0, 1)])
+@pytest.mark.parametrize("M", [70, 66000])
+def test_gemm_row_alignment(M, N, c_off, r_off, width):
+    """Rows of C and of the residual at every alignment (accesses of `width` elements), in small and
+    in large tiles, with each epilogue; the residual also in place."""
+    rows = np.concatenate([np.arange(70), np.arange(0, M, 1021), np.arange(M - 70, M)])
+    for epi, in_place in ((0, False), (1, False), (1, r_off == c_off), (2, False)):
+        if epi != 2 or N % 2 == 0:
+            _sampled_gemm(M, N, 72, epi, rows, c_off, r_off, in_place)
+
+
 def test_swiglu_in_single_precision():
     """SiLU(gate) up to 2^-21: expf's 2^-23, and 2^-24 each for 1 + e, the division and the product come to
     5 x 2^-24.  The products are zero, so gate and up are the fp32 biases; up puts each result 2^-21 to
