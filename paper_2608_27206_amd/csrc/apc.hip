@@ -1,11 +1,13 @@
 // APC (Section 3.2, "Condense"): per-patch information density of a uint8 image and
 // the bicubic resize by sqrt(r) per side (Appendix implementation details).
 //
-// Density, four launches (all HBM/L2-bound, fixed reduction orders -> deterministic):
-//   apc_patch_pass<0>  per patch-strip tile (256 or 1,024 threads): ||f_i|| -> 1/||f_i|| (from exact integer sums of
-//                      the bytes and their squares), and the tile's partial sum of
-//                      T_i = f_i/||f_i|| over its patches (one 588-vector per tile)
-//   apc_reduce_c       sum of the tile partials per component -> sum_i T_i
+// Density, four launches, three for images of up to 64 tiles (fixed reduction orders ->
+// deterministic):
+//   apc_patch_pass<0>  per patch-strip tile (256 or 1,024 threads): ||f_i|| -> 1/||f_i|| (from
+//                      exact integer sums of the bytes and their squares), and the tile's partial
+//                      sum of T_i = f_i/||f_i|| over its patches (one 588-vector per tile)
+//   apc_reduce_c       sum of the tile partials per component -> sum_i T_i (pass 1 sums them
+//                      itself for up to 64 tiles)
 //   apc_patch_pass<1>  c = mean T_i, phi = ||c||^2 (equal to Eq. 1's mean pairwise cosine),
 //                      rho_g = 1 - phi (Eq. 2) and c_hat = c/||c||, recomputed by every
 //                      workgroup from the sums; then d_i = ||T_i - c_hat|| (the image is
@@ -25,8 +27,9 @@ namespace {
 
 constexpr int kPatchesPerTile = 64;   // patches of one patch row per workgroup
 // With at most this many tiles the second patch pass sums the tiles' partials itself instead of
-// reading apc_reduce_c's sums: a launch less (448 x 448, 32 tiles: 18.4 -> 15.9 us per call), at two
-// round trips of loads more than that for 32 tiles.
+// reading apc_reduce_c's sums: a launch less, for loads that grow with the tiles.  Own sums against
+// apc_reduce_c, us per call: 16 tiles 14.9 / 18.6, 32 16.6 / 18.5, 56 20.6 / 21.4, 64 21.6 / 21.7, 80 23.6 /
+// 22.5, 144 26.7 / 23.0.
 constexpr int kOwnSums = 64;
 constexpr int kMaxPatch = 16;
 
@@ -68,7 +71,7 @@ __device__ __noinline__ uint32_t load_dword_bytes(__amdgpu_buffer_rsrc_t rs, uns
   return v;
 }
 
-// Stages the tile's pixels (P rows x up to TP patches) in LDS as bytes, through 16-byte loads at
+// Stages the tile's pixels (P rows x up to 64 patches) in LDS as bytes, through 16-byte loads at
 // dword addresses of a range-checked buffer (reads never leave the image): one per thread and
 // row (a row of 64 patches of 16 has 193), all rows in flight before the LDS writes.  Row r of the
 // tile starts at byte shift[r] of its LDS row.
@@ -696,6 +699,7 @@ __global__ __launch_bounds__(1024) void apc_reduce_c(const DensityParams p) {
   }
 }
 
+// Calls with 16 / 64 slices: 80 tiles 21.9 / 22.6 us, 256 23.5 / 23.2, 300 30.1 / 29.4, 770 41.8 / 40.5.
 pace_status_t launch_reduce_c(const DensityParams& p, hipStream_t stream) {
   if (p.n_tiles <= 256) hipLaunchKernelGGL((apc_reduce_c<16>), dim3((p.D + 63) / 64), dim3(1024), 0, stream, p);
   else hipLaunchKernelGGL((apc_reduce_c<64>), dim3((p.D + 15) / 16), dim3(1024), 0, stream, p);
@@ -962,12 +966,13 @@ __device__ __forceinline__ int make_taps(int o, int n, int m, int slots, float* 
   return lo + j0;
 }
 
-// make_taps spread over a row of 16 lanes, lane j holding candidate j (slots <= 16): every
+// make_taps spread over a row of 16 lanes, lane j < SLOTS holding candidate j: every
 // lane of the row evaluates one weight, the row's sum comes from a butterfly (every lane ends
 // with the same bits) and the first and last nonzero candidates from a ballot.  The same
 // weights, lo and count as make_taps up to the order of the normalising sum.  All 64 lanes
-// of the wave must call it together (`valid` false for rows of 16 with no coordinate); the
-// distance numerator is formed in 32 bits when 2 n m fits, which makes the same float.
+// of the wave must call it together (`valid` false for rows of 16 with no coordinate).  `small`
+// (the host's word that the axis allows it): the distance numerator from 24-bit factors in 32 bits,
+// which makes the same float as 64.
 // keys_cubic without branches (both pieces evaluated, then selected): the same values
 __device__ __forceinline__ float keys_cubic_sel(float x) {
   x = fabsf(x);
@@ -975,9 +980,10 @@ __device__ __forceinline__ float keys_cubic_sel(float x) {
   const float b = ((-0.5f * x + 2.5f) * x - 4.f) * x + 2.f;
   return x <= 1.f ? a : (x < 2.f ? b : 0.f);
 }
-// ratio = n / m and inv_den = 1 / (2 max(n, m)) come from the host.  The first candidate lo may
-// sit one sample off the one make_taps finds (the centre rounds differently), but the 16
-// candidates still cover the support, whose weights come from the same exact numerators.
+// ratio = n / m and inv_den = 1 / (2 max(n, m)) come from the host.  The support holds at most NT
+// samples; candidate 0 lies two before the first of them, or one or three (the centre rounds
+// differently than in make_taps).  SLOTS >= NT + 3 candidates cover the support then, and its
+// weights come from the same exact numerators.
 template <int SLOTS>
 __device__ __forceinline__ void make_taps_row16(int o, bool valid, int n, int m, bool small, float ratio,
                                                 float inv_den, float* w_out, int* lo_out, int* count_out) {
@@ -1015,7 +1021,7 @@ __device__ __forceinline__ void make_taps_row16(int o, bool valid, int n, int m,
 // weights past a count being zero (adding 0 * x leaves every sum bit for bit as it was).  Same
 // arithmetic, in the same order, as apc_resize.
 //   Bound: VALU (a conversion and an FMA per tap and byte, and the taps and staging of the tile).
-// On the 4K frame halved per side, 37.2 -> 25.9 us per call against 16-row tiles of 256 threads with
+// On the 4K frame halved per side, 34.7 -> 24.0 us per call against 16-row tiles of 256 threads with
 // run-time tap counts, dword staging with a test per load, and 64-bit tap distances: unrolled
 // taps in the vertical pass, 16-byte staging, 24-bit products and fewer taps and halo rows per
 // output pixel (16 rows with all else equal: 28.0 us; at 1.4x 44.4 against 32.3).
@@ -1025,6 +1031,7 @@ __global__ __launch_bounds__(kRsRegThreads) void apc_resize_reg(const ResizePara
   constexpr int ND = (3 * NT + 3) / 4 + 1;   // dwords covering 3 NT bytes at any byte shift
   constexpr int kTx = 32;                    // output columns per workgroup
   constexpr int SLOTS = (NT + 6) / 4 * 4;    // weights per coordinate: 8, 12 or 16
+  static_assert(SLOTS >= NT + 3 && SLOTS <= 16, "candidates of a coordinate (see make_taps_row16)");
   extern __shared__ __align__(16) float sm[];
   float* wx = sm;                                    // [kTx][SLOTS]
   float* wy = wx + kTx * SLOTS;                      // [TY][SLOTS]
@@ -1312,13 +1319,15 @@ __global__ __launch_bounds__(kRsThreads) void apc_resize(const ResizeParams p) {
   }
 }
 
-// A patch pass over the image's tiles.  With fewer tiles than CUs a workgroup has its CU to itself
+// A patch pass over the image's tiles.  With no more tiles than CUs a workgroup has its CU to itself
 // and takes 1,024 threads: its phases are chains of memory and LDS round trips that more threads
 // shorten (448 x 448, 32 tiles: passes 7.5 + 7.8 us with 256 threads, 6.0 + 5.4 with 1,024); with
-// more, 256 threads (2156 x 3836, 770 tiles: 13.2 + 12.2 us against 16.0 + 14.4).
+// more, 256 threads (2156 x 3836, 770 tiles: 13.2 + 12.2 us against 16.0 + 14.4).  Around the line, calls
+// at patch 14 with 256 / 1,024 threads: 224 tiles 26.0 / 23.8 us, 256 26.0 / 24.0, 280 31.3 / 31.3, 300 29.3 /
+// 30.8, 512 31.2 / 32.7.
 template <int PASS>
 pace_status_t launch_patch_pass(const DensityParams& p, hipStream_t stream) {
-  const int nt = p.n_tiles < 256 ? 1024 : 256;
+  const int nt = p.n_tiles <= 256 ? 1024 : 256;
   // pixels, 1/norms and c_hat (pass 1); or the parts of the tile's sum (pass 0, at most 8 floats a
   // thread)
   size_t lds = (static_cast<size_t>(p.P) * p.row_dwords + kPatchesPerTile +

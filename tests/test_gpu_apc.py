@@ -131,7 +131,7 @@ def test_density_random_shapes(case):
 
 
 @pytest.mark.parametrize("patch,gh,gw", [(1, 40, 37), (2, 23, 31), (5, 17, 29), (3, 64, 70), (11, 9, 67),
-                                         # 256 tiles and more: the passes with 256 threads per tile
+                                         # above 256 tiles, the passes with 256 threads per tile; 256 tiles
                                          (1, 301, 70), (3, 257, 65), (13, 261, 1), (16, 256, 3)])
 def test_density_small_and_odd_patches(patch, gh, gw):
     """Patch sizes whose rows split unevenly over a patch's four threads (3P bytes: 3, 6, 15, 9
