@@ -346,10 +346,11 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_fwd(const FwdParams
     const int rem = pos - level * nseg * p.heads;
     qt = p.nqt - 1 - level;
     const int sl = div_fast(rem, p.by_heads);
-    // The workgroups of an XCD go to its four shader engines in turn.  Where the number of segments is
-    // even, those of one segment would come to the same one or two in every level, and a long
-    // segment among short ones to a quarter or half of the CUs: the segments move on by one every
-    // level or two (8 / 2 heads, 4,064 tokens beside three of 164: 135 -> 62 us, beside two 61).
+    // By the timings, the workgroups of an XCD go to its four shader engines in turn: where the number
+    // of segments is even, those of one segment would come to the same one or two in every level,
+    // and a long segment among short ones to a quarter or half of the CUs.  So the segments move on
+    // by one every level or two (8 / 2 heads, 4,064 tokens beside three of 164: 135 -> 62 us, beside
+    // two 61).
     int sr = sl;
     if (p.rotate) {
       sr += (nseg & 3) == 0 ? level & 3 : (nseg & 1) == 0 ? (level >> 1) & 1 : 0;
@@ -1747,10 +1748,11 @@ void launch_fwd(const FwdParams& fp, int max_seglen, dim3 grid, hipStream_t stre
 }
 
 // The order of the causal forward's workgroups (see attn_fwd).  Segments are taken together in groups of
-// so many that an XCD works on about eight K/V streams at a time: beyond that its workgroups of one
+// so many that an XCD works on about four K/V streams at a time: beyond that its workgroups of one
 // stream lie too far apart to share it in L2 (16 sequences of 4,128 tokens, 16 / 16 heads, two KV heads per
-// XCD: all at once 1,330 us, eight sequences 1,172, four 1,121).  But no fewer than about four rounds of
-// workgroups, of which the long rows of the last group would otherwise be a large part.
+// XCD: all at once 1,335 us, eight sequences 1,172, four 1,121, two 1,110).  But no fewer than one and a
+// half rounds of workgroups at two per CU, and in groups of even sizes: the long rows of a small last
+// group start late (eight sequences of 1,183 tokens in seven and one 77 us, together 68).
 inline void causal_order(FwdParams& fp, int max_seglen) {
   fp.xcd_classes = fp.Hkv % 8 == 0 ? 8 : fp.Hkv % 4 == 0 ? 4 : fp.Hkv % 2 == 0 ? 2 : 1;
   fp.heads = fp.Hq / fp.xcd_classes;
