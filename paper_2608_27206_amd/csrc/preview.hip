@@ -442,8 +442,8 @@ void launch_tile(GemmParams p, int nz, hipStream_t stream) {
 // us at 1,024 rows).  The rows go to whichever of these is the shortest: large tiles alone, small ones alone,
 // or the full rounds in large and the remaining rows in small tiles; large ones alone also if they
 // cost 0.15 more (20,000 rows: two rounds 78.3 us, one and 0.9 of one in small tiles 84.3, as the second
-// launch starts in the first one's idle end), and two launches only if they cost 0.1 less.  Over 149
-// products (1 to 42,196 rows; N = 100 to 6,854; K = 592 to 3,424) the choice is within 6% of the best of
+// launch starts in the first one's idle end), and two launches only if they cost 0.1 less.  Over 168
+// products (1 to 42,196 rows; N = 100 to 6,854; K = 592 to 3,424) the choice is within 7% of the best of
 // the three.
 pace_status_t launch_gemm(GemmParams p, int nz, hipStream_t stream) {
   const int nc = p.mode == kEpiSwiglu ? p.N / 2 : p.N;
